@@ -11,33 +11,22 @@
 //   W12hat[f] (C x K) = W1hat[f] (C x J) * W2hat[f] (J x K).
 //
 // Two implementations, both staging 16-deep slices of the reduction for one
-// output tile through LDS as separate real and imaginary planes, with the
-// next slice loaded into registers while the current one is consumed:
-//  * vector ALU: 64 x 64 complex tile per 256-lane workgroup, 4 x 4 complex
-//    accumulators per lane, four real multiply-adds per complex one;
-//  * fp32 matrix cores (v_mfma_f32_16x16x4f32): 128 x 64 (or 96 x 64, or
-//    64 x 96) complex tile per workgroup, persistent workgroups walking the
-//    tiles in XCD-local rounds, operands read through buffer resources, LDS
-//    slices laid out so that one 16-byte read serves four matrix-core steps,
-//    and three real products per complex multiply-add (Gauss's form).
+// output tile through LDS, with the next slice loaded into registers while
+// the current one is consumed:
+//  * vector ALU: real and imaginary planes, 64 x 64 complex tile per 256-lane
+//    workgroup, 4 x 4 complex accumulators per lane, four real multiply-adds
+//    per complex one;
+//  * bf16 matrix cores (v_mfma_f32_16x16x32_bf16) on operands split exactly
+//    into three bf16 pieces each, with fp32 accumulation: 16 x 64 to 128 x 128
+//    complex tiles per workgroup, persistent workgroups walking the tiles in
+//    XCD-local rounds, operands read through buffer resources.
 #include <algorithm>
+#include <atomic>
+#include <cmath>
 
 #include "buffer_io.hpp"
 #include "oaa_internal.hpp"
-
-// Minimum waves per SIMD asked of the register allocator for the
-// matrix-core kernel, and its 16-column blocks per wave (tile width / 32);
-// overridable at build time for tuning sweeps.
-#ifndef OAA_WAVES_GEMM
-#define OAA_WAVES_GEMM 2
-#endif
-#ifndef OAA_GEMM_NB
-#define OAA_GEMM_NB 2
-#endif
-// Matrix-core step of a slice after which the next slice goes to LDS (0..3).
-#ifndef OAA_GEMM_STORE_STEP
-#define OAA_GEMM_STORE_STEP 2
-#endif
+#include "tile_common.hpp"
 
 namespace oaa {
 
@@ -182,105 +171,114 @@ __global__ void __launch_bounds__(kThreads) cgemm_valu_kernel(GemmParams p) {
 // matrix-core implementation
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-// LDS layout of an operand slice: [row][k'] with separate real and imaginary
-// planes, k' = (k % 4) * (kKC / 4) + k / 4. The matrix-core step s of a slice
-// uses reduction index k = 4 s + (lane / 16), so one 16-byte read gives a
-// lane its values for all four steps of a slice. Rows are padded to kLdk
-// floats, which keeps those reads and the stores below free of bank
-// conflicts (at most two-way for k-contiguous operands).
-constexpr int kLdk = kKC + 4;
-__device__ __forceinline__ constexpr int kperm(int k) { return (k % 4) * (kKC / 4) + k / 4; }
+// A complex value as three complex bf16 pieces, each packed (re low, im
+// high): x = p0 + p1 + p2 exactly, since each rounding to nearest leaves a
+// remainder of at most 16 and then 8 significant bits of the 24.
+__device__ __forceinline__ void split3(float2 x, unsigned& p0, unsigned& p1, unsigned& p2) {
+  auto pack = [](float a, float b) {
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(floatx2{a, b}, bf16x2));
+  };
+  auto lo = [](unsigned u) { return __builtin_bit_cast(float, u << 16); };
+  auto hi = [](unsigned u) { return __builtin_bit_cast(float, u & 0xffff0000u); };
+  p0 = pack(x.x, x.y);
+  const float r1 = x.x - lo(p0), i1 = x.y - hi(p0);
+  p1 = pack(r1, i1);
+  p2 = pack(r1 - lo(p1), i1 - hi(p1));
+}
+
+// LDS image of an operand's ROWS x kKC slice, one per piece: rows of four
+// 16-byte quads, quad q holding reduction indices 4q .. 4q + 3 as packed
+// complex pieces, stored at quad q ^ ((row / 4) % 4) of the row. The 16
+// lanes that read one quad of 16 consecutive rows, and the lanes that write
+// it, then fall on all 64 banks.
+__device__ __forceinline__ constexpr int quad_at(int row, int q) {
+  return row * 4 + (q ^ ((row >> 1) & 3) ^ ((row >> 3) & 1));
+}
 
 // One operand's ROWS x kKC slices, read through a buffer resource over one
 // bin's matrix; element (row, k) is at k*ld + row (ROW_CONTIG) or row*ld + k.
-// Per tile, each lane computes the byte offsets of its elements relative to
-// the slice start (an offset past the resource for rows outside the matrix,
-// which the hardware reads as zero); per slice only a scalar offset changes.
-//  * ROW_CONTIG: lane t < G*ROWS (G = 256 / ROWS, 2 or 4) takes row t % ROWS
-//    and reduction indices t / ROWS + G i; loads are coalesced along rows,
-//    and each lane's values form runs of four in k', stored with 16-byte
-//    writes. The resource ends at the tile's reduction bound.
-//  * k-contiguous: lane t takes k = t % kKC of rows t / kKC + (256/kKC) i;
-//    loads are coalesced along k; elements past the reduction bound are
-//    redirected out of range per slice.
-template <bool ROW_CONTIG, int ROWS>
+// A task is a quad of one row: four loads, split into pieces and written to
+// LDS as three quads. Lanes run along the rows (ROW_CONTIG) or along the
+// four quads of a row, so that loads are coalesced. Elements outside the
+// matrix or past the reduction bound get an offset beyond the resource, which
+// the hardware reads as zero. Lane FIRST takes the first task, so that two
+// small operands are staged by different waves.
+template <bool ROW_CONTIG, int ROWS, int THREADS, int FIRST>
 struct Operand {
-  static constexpr int G = ROW_CONTIG ? (kThreads / ROWS >= 4 ? 4 : 2) : 1;
-  static constexpr int PER = ROW_CONTIG ? kKC / G : ROWS * kKC / kThreads;
-  static_assert(!ROW_CONTIG || (ROWS == 64 || ROWS == 96 || ROWS == 128), "row tile");
+  static constexpr int TASKS = ROWS * 4, PER = (TASKS + THREADS - 1) / THREADS;
+  static constexpr bool WHOLE = TASKS % THREADS == 0;  // every lane has PER tasks
   unsigned voff[PER];
-  float2 v[PER];
-  int kl;  // k-contiguous: this lane's reduction index within a slice
+  float2 v[PER][4];
 
-  __device__ __forceinline__ bool active() const {
-    return !ROW_CONTIG || int(threadIdx.x) < G * ROWS;
+  __device__ __forceinline__ static int task(int i) {
+    return int((threadIdx.x + unsigned(THREADS - FIRST)) % unsigned(THREADS)) + THREADS * i;
   }
+  __device__ __forceinline__ static int row_of(int t) { return ROW_CONTIG ? t % ROWS : t / 4; }
+  __device__ __forceinline__ static int quad_of(int t) { return ROW_CONTIG ? t / ROWS : t % 4; }
 
   __device__ __forceinline__ void set_tile(int r0, int nrows, unsigned ld) {
-    const int t = threadIdx.x;
-    if (ROW_CONTIG) {
-      const int r = r0 + t % ROWS, kg = t / ROWS;
-      const bool ok = r < nrows && active();
 #pragma unroll
-      for (int i = 0; i < PER; ++i) voff[i] = ok ? (unsigned(kg + G * i) * ld + unsigned(r)) * 8u : kOutOfRange;
-    } else {
-      kl = t % kKC;
-#pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        const int r = r0 + t / kKC + (kThreads / kKC) * i;
-        voff[i] = r < nrows ? (unsigned(r) * ld + unsigned(kl)) * 8u : kOutOfRange;
-      }
+    for (int i = 0; i < PER; ++i) {
+      const int t = task(i), r = r0 + row_of(t), k = 4 * quad_of(t);
+      const bool ok = r < nrows && (WHOLE || t < TASKS);
+      voff[i] = ok ? (ROW_CONTIG ? unsigned(k) * ld + unsigned(r) : unsigned(r) * ld + unsigned(k)) * 8u : kOutOfRange;
     }
   }
 
   // slice starting at reduction index k0 of a tile whose reduction ends at
   // ke, from a matrix of `elems` elements at base. The resource starts at the
-  // slice, so that the hardware's range check sees only the lane offsets.
+  // slice, so that the hardware's range check sees only the lane offsets
+  // (ROW_CONTIG: it also ends at the reduction bound). An offset out of range
+  // stays so when 3 ld elements are added (ld < 2^25, see mfma_fits).
   __device__ __forceinline__ void load(const float2* base, size_t elems, unsigned ld, int k0, int ke) {
     if (ROW_CONTIG) {
       const __amdgpu_buffer_rsrc_t rs = buffer_resource(base + size_t(k0) * ld, unsigned(ke - k0) * ld * 8u);
 #pragma unroll
       for (int i = 0; i < PER; ++i)
-        v[i] = buffer_load_f2(rs, voff[i]);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[i][j] = buffer_load_f2(rs, voff[i] + unsigned(j) * ld * 8u);
     } else {
       const __amdgpu_buffer_rsrc_t rs = buffer_resource(base + k0, unsigned(elems - size_t(k0)) * 8u);
-      const bool kok = kl < ke - k0;
 #pragma unroll
-      for (int i = 0; i < PER; ++i)
-        v[i] = buffer_load_f2(rs, kok ? voff[i] : kOutOfRange);
+      for (int i = 0; i < PER; ++i) {
+        const int k = 4 * quad_of(task(i));
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          v[i][j] = buffer_load_f2(rs, k + j < ke - k0 ? voff[i] + unsigned(j) * 8u : kOutOfRange);
+      }
     }
   }
 
-  __device__ __forceinline__ void store(float (*re)[kLdk], float (*im)[kLdk], bool conj) const {
-    const int t = threadIdx.x;
-    if (ROW_CONTIG) {
-      if (!active()) return;
-      const int r = t % ROWS, kg = t / ROWS;
-      // values i = q + (4/G) m, m < 4, share k % 4 = (kg + G q) % 4 and have k / 4 = m + const
+  __device__ __forceinline__ void store(uintx4* lds) const {
 #pragma unroll
-      for (int q = 0; q < 4 / G; ++q) {
-        const int kp = kperm(kg + G * q);
-        floatx4 xr, xi;
+    for (int i = 0; i < PER; ++i) {
+      const int t = task(i);
+      if (!WHOLE && t >= TASKS) continue;
+      uintx4 q0, q1, q2;
 #pragma unroll
-        for (int m = 0; m < 4; ++m) {
-          xr[m] = v[q + (4 / G) * m].x;
-          xi[m] = conj ? -v[q + (4 / G) * m].y : v[q + (4 / G) * m].y;
-        }
-        *reinterpret_cast<floatx4*>(&re[r][kp]) = xr;
-        *reinterpret_cast<floatx4*>(&im[r][kp]) = xi;
+      for (int j = 0; j < 4; ++j) {
+        unsigned a, b, c;
+        split3(v[i][j], a, b, c);
+        q0[j] = a;
+        q1[j] = b;
+        q2[j] = c;
       }
-    } else {
-      const int kp = kperm(kl);
-#pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        const int r = t / kKC + (kThreads / kKC) * i;
-        re[r][kp] = v[i].x;
-        im[r][kp] = conj ? -v[i].y : v[i].y;
-      }
+      uintx4* at = lds + quad_at(row_of(t), quad_of(t));
+      at[0] = q0;
+      at[TASKS] = q1;
+      at[2 * TASKS] = q2;
     }
   }
 };
+
+__device__ __forceinline__ floatx4 mfma(bf16x8 a, bf16x8 b, floatx4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
 
 // One output tile of the logical tile sequence: bin, split, row tile, column
 // tile (fastest).
@@ -302,27 +300,47 @@ __device__ __forceinline__ MfmaTile mfma_tile(const GemmParams& p, unsigned t, u
   return c;
 }
 
+// LDS of a tile: two buffers of three pieces of both operands' slices.
+constexpr size_t mfma_lds_bytes(int TM, int TN) { return size_t(TM + TN) * 4 * 16 * 3 * 2; }
+
 // Persistent matrix-core contraction. MB x NB blocks of 16 x 16 per wave,
-// waves in a 2 x 2 grid: tile (32*MB) x (32*NB) complex per workgroup. The
-// grid (a multiple of 8 workgroups) walks the logical tile sequence in
+// waves in a WM x WN grid: tile (16 WM MB) x (16 WN NB) complex per workgroup.
+// The grid (a multiple of 8 workgroups) walks the logical tile sequence in
 // rounds; in each round the workgroups of one XCD take consecutive tiles, so
 // that tiles sharing operand slices share that XCD's L2. Each workgroup
 // streams the reduction slices of all its tiles through one double-buffered
 // LDS pipeline: the first slice of its next tile is loaded while the last
 // slice of the current one is multiplied.
 //
-// Each complex multiply-add uses three real products (Gauss): with
-// p1 = sum ar br, p2 = sum ai bi and p3 = sum (ar + ai)(br + bi), the result
-// is re = p1 - p2, im = p3 - p1 - p2.
-template <int MB, int NB, bool AT, bool AC, bool BT, bool BC>
-__global__ void __launch_bounds__(kThreads, OAA_WAVES_GEMM) cgemm_mfma_kernel(GemmParams p, unsigned ntiles) {
-  constexpr int TM = 32 * MB, TN = 32 * NB;
-  __shared__ __attribute__((aligned(16))) float Asr[2][TM][kLdk], Asi[2][TM][kLdk];
-  __shared__ __attribute__((aligned(16))) float Bsr[2][TN][kLdk], Bsi[2][TN][kLdk];
+// The complex product is a real one of twice the depth: with rows (ar, ai)
+// interleaved, the real part is their product with columns (br, -bi) and the
+// imaginary part with (bi, br) (conjugated a: (br, bi) and (bi, -br)), both
+// made from the packed (br, bi) in registers. Of the nine products of the
+// pieces, the six of order up to 2^-16 are taken; the three left out are
+// below 2^-24 of the product, under fp32's own rounding of it. Each slice's
+// products are summed in accumulators of their own, the smallest first, and
+// added to the tile's once: adding all six straight to the tile's left a
+// reduction over 256 tiles at 4.9e-7 relative error against 64 bits, where
+// this leaves 3.6e-7 and three fp32 products (Gauss's form, on the fp32
+// matrix cores) left 4.1e-7.
+//
+// Bound by power at large sizes: the clock falls to 1.5 - 1.9 GHz, and
+// neither deeper prefetch, nor three workgroups per CU on a single buffer,
+// nor the split interleaved with the products moved the 1.05 PFLOP/s of bf16
+// that it runs at. The large-kernel layer's three products take 0.78, 0.69
+// and 0.70 ms against 0.85, 0.86 and 0.74 on the fp32 matrix cores, those of
+// 128 channels at 56 x 56 0.21 against 0.28 ms.
+template <int WM, int WN, int MB, int NB, bool AT, bool AC, bool BT>
+__global__ void __launch_bounds__(64 * WM * WN, 2) cgemm_mfma_kernel(GemmParams p, unsigned ntiles) {
+  constexpr int TM = 16 * WM * MB, TN = 16 * WN * NB, THREADS = 64 * WM * WN;
+  constexpr int QA = TM * 4, QB = TN * 4;  // quads per piece
+  extern __shared__ uintx4 lds[];          // [2][3][QA] then [2][3][QB]
+  uintx4* const ldsb = lds + 6 * QA;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = (wave >> 1) * 16 * MB, wn = (wave & 1) * 16 * NB;
+  const int wm = (wave / WN) * 16 * MB, wn = (wave % WN) * 16 * NB;
   const int lr = lane & 15;  // operand row (A) / column (B) within a 16-block
-  const int lk = lane >> 4;  // reduction index within a matrix-core step
+  const int lk = lane >> 4;  // quad of the slice
+  const int fa = quad_at(wm + lr, lk), fb = quad_at(wn + lr, lk);
 
   const unsigned tiles_m = (p.M + TM - 1) / TM, tiles_n = (p.N + TN - 1) / TN;
   const unsigned nwg = gridDim.x;
@@ -335,8 +353,8 @@ __global__ void __launch_bounds__(kThreads, OAA_WAVES_GEMM) cgemm_mfma_kernel(Ge
   MfmaTile nx = cur;
   int lkk = ck;
 
-  Operand<AT, TM> sa;
-  Operand<!BT, TN> sb;
+  Operand<AT, TM, THREADS, 0> sa;
+  Operand<!BT, TN, THREADS, (TM * 4) % THREADS> sb;
   auto set_tile = [&](const MfmaTile& t) {
     sa.set_tile(t.m0, p.M, unsigned(p.lda));
     sb.set_tile(t.n0, p.N, unsigned(p.ldb));
@@ -359,20 +377,19 @@ __global__ void __launch_bounds__(kThreads, OAA_WAVES_GEMM) cgemm_mfma_kernel(Ge
 
   set_tile(nx);
   load_slice(nx, lkk);
-  sa.store(Asr[0], Asi[0], AC);
-  sb.store(Bsr[0], Bsi[0], BC);
+  sa.store(lds);
+  sb.store(ldsb);
   advance(lt, nx, lkk, true);
   __syncthreads();
 
-  floatx4 p1[MB][NB], p2[MB][NB], p3[MB][NB];
+  floatx4 cr[MB][NB], ci[MB][NB];
   auto zero = [&]() {
 #pragma unroll
     for (int i = 0; i < MB; ++i)
 #pragma unroll
       for (int j = 0; j < NB; ++j) {
-        p1[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-        p2[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-        p3[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+        cr[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+        ci[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
       }
   };
   zero();
@@ -381,50 +398,95 @@ __global__ void __launch_bounds__(kThreads, OAA_WAVES_GEMM) cgemm_mfma_kernel(Ge
   for (;;) {
     const bool more = lt < ntiles;
     if (more) load_slice(nx, lkk);
-    floatx4 Ar[MB], Ai[MB], Br[NB], Bi[NB];
+    const uintx4* la = lds + buf * 3 * QA + fa;
+    const uintx4* lb = ldsb + buf * 3 * QB + fb;
+    // operand fragments: rows i of A; columns j of the real part, (br, -bi) or
+    // with a conjugated (br, bi), and of the imaginary part, (bi, br) or (bi, -br)
+    auto rows = [&](int i, bf16x8(&a)[3]) {
 #pragma unroll
-    for (int i = 0; i < MB; ++i) {
-      Ar[i] = *reinterpret_cast<const floatx4*>(&Asr[buf][wm + 16 * i + lr][4 * lk]);
-      Ai[i] = *reinterpret_cast<const floatx4*>(&Asi[buf][wm + 16 * i + lr][4 * lk]);
-    }
+      for (int q = 0; q < 3; ++q) a[q] = __builtin_bit_cast(bf16x8, la[q * QA + 64 * i]);
+    };
+    auto columns = [&](int j, bf16x8(&br)[3], bf16x8(&bi)[3]) {
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      Br[j] = *reinterpret_cast<const floatx4*>(&Bsr[buf][wn + 16 * j + lr][4 * lk]);
-      Bi[j] = *reinterpret_cast<const floatx4*>(&Bsi[buf][wn + 16 * j + lr][4 * lk]);
-    }
-    // The wave issues its matrix-core products at raised priority, so that
-    // the arbiter keeps them flowing while the other waves of the SIMD load
-    // and store; the next slice goes to LDS half way through (the buffer it
-    // overwrites was released by the previous barrier).
-    __builtin_amdgcn_s_setprio(1);
+      for (int q = 0; q < 3; ++q) {
+        const uintx4 b = lb[q * QB + 64 * j];
+        uintx4 re, im;
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      if (s == OAA_GEMM_STORE_STEP && more) {
-        sa.store(Asr[buf ^ 1], Asi[buf ^ 1], AC);
-        sb.store(Bsr[buf ^ 1], Bsi[buf ^ 1], BC);
+        for (int e = 0; e < 4; ++e) {
+          const unsigned swapped = __builtin_amdgcn_alignbit(b[e], b[e], 16);
+          re[e] = AC ? b[e] : b[e] ^ 0x80000000u;
+          im[e] = AC ? swapped ^ 0x80000000u : swapped;
+        }
+        br[q] = __builtin_bit_cast(bf16x8, re);
+        bi[q] = __builtin_bit_cast(bf16x8, im);
       }
-      float as[MB], bs[NB];
+    };
+    // half way through the products, the slice loaded at their start goes to the
+    // buffer that the previous barrier released
+    auto next_slice = [&]() {
+      if (!more) return;
+      sa.store(lds + (buf ^ 1) * 3 * QA);
+      sb.store(ldsb + (buf ^ 1) * 3 * QB);
+    };
+    constexpr bool A_STAYS = 20 * MB + 24 < 32 * NB + 12;  // registers of either order
+    if constexpr (A_STAYS) {
+      bf16x8 a[MB][3];
 #pragma unroll
-      for (int i = 0; i < MB; ++i) as[i] = Ar[i][s] + Ai[i][s];
+      for (int i = 0; i < MB; ++i) rows(i, a[i]);
+      __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-      for (int j = 0; j < NB; ++j) bs[j] = Br[j][s] + Bi[j][s];
-      // three independent sweeps, so that dependent accumulations are
-      // MB*NB instructions apart
+      for (int j = 0; j < NB; ++j) {
+        if (j == (NB + 1) / 2) next_slice();
+        bf16x8 br[3], bi[3];
+        columns(j, br, bi);
+        floatx4 tr[MB], ti[MB];
 #pragma unroll
-      for (int i = 0; i < MB; ++i)
+        for (int i = 0; i < MB; ++i) tr[i] = ti[i] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int j = 0; j < NB; ++j)
-          p1[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(Ar[i][s], Br[j][s], p1[i][j], 0, 0, 0);
+        for (int order = 2; order >= 0; --order)
 #pragma unroll
-      for (int i = 0; i < MB; ++i)
+          for (int pa = order; pa >= 0; --pa)
 #pragma unroll
-        for (int j = 0; j < NB; ++j)
-          p3[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(as[i], bs[j], p3[i][j], 0, 0, 0);
+            for (int i = 0; i < MB; ++i) {
+              tr[i] = mfma(a[i][pa], br[order - pa], tr[i]);
+              ti[i] = mfma(a[i][pa], bi[order - pa], ti[i]);
+            }
 #pragma unroll
-      for (int i = 0; i < MB; ++i)
+        for (int i = 0; i < MB; ++i) {
+          cr[i][j] += tr[i];
+          ci[i][j] += ti[i];
+        }
+      }
+      if (NB == 1) next_slice();
+    } else {
+      bf16x8 br[NB][3], bi[NB][3];
 #pragma unroll
-        for (int j = 0; j < NB; ++j)
-          p2[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(Ai[i][s], Bi[j][s], p2[i][j], 0, 0, 0);
+      for (int j = 0; j < NB; ++j) columns(j, br[j], bi[j]);
+      __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int i = 0; i < MB; ++i) {
+        if (i == (MB + 1) / 2) next_slice();
+        bf16x8 a[3];
+        rows(i, a);
+        floatx4 tr[NB], ti[NB];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) tr[j] = ti[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int order = 2; order >= 0; --order)
+#pragma unroll
+          for (int pa = order; pa >= 0; --pa)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+              tr[j] = mfma(a[pa], br[j][order - pa], tr[j]);
+              ti[j] = mfma(a[pa], bi[j][order - pa], ti[j]);
+            }
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+          cr[i][j] += tr[j];
+          ci[i][j] += ti[j];
+        }
+      }
+      if (MB == 1) next_slice();
     }
     __builtin_amdgcn_s_setprio(0);
     if (ck + kKC >= cur.ke) {
@@ -433,9 +495,6 @@ __global__ void __launch_bounds__(kThreads, OAA_WAVES_GEMM) cgemm_mfma_kernel(Ge
       float2* Cm = p.C + size_t(cur.f) * p.c_fstride + size_t(cur.split) * p.c_sstride;
       const unsigned ldc = unsigned(p.ldc);
       const int mb = cur.m0 + wm + 4 * lk, nb = cur.n0 + wn + lr;
-      auto result = [&](int i, int j, int r) {
-        return make_float2(p1[i][j][r] - p2[i][j][r], p3[i][j][r] - p1[i][j][r] - p2[i][j][r]);
-      };
       if (cur.m0 + TM <= p.M && cur.n0 + TN <= p.N) {
 #pragma unroll
         for (int i = 0; i < MB; ++i)
@@ -443,7 +502,7 @@ __global__ void __launch_bounds__(kThreads, OAA_WAVES_GEMM) cgemm_mfma_kernel(Ge
           for (int r = 0; r < 4; ++r) {
             float2* row = Cm + unsigned(mb + 16 * i + r) * ldc + unsigned(nb);
 #pragma unroll
-            for (int j = 0; j < NB; ++j) row[16 * j] = result(i, j, r);
+            for (int j = 0; j < NB; ++j) row[16 * j] = make_float2(cr[i][j][r], ci[i][j][r]);
           }
       } else {
 #pragma unroll
@@ -454,7 +513,7 @@ __global__ void __launch_bounds__(kThreads, OAA_WAVES_GEMM) cgemm_mfma_kernel(Ge
             float2* row = Cm + unsigned(m) * ldc + unsigned(nb);
 #pragma unroll
             for (int j = 0; j < NB; ++j)
-              if (m < p.M && nb + 16 * j < p.N) row[16 * j] = result(i, j, r);
+              if (m < p.M && nb + 16 * j < p.N) row[16 * j] = make_float2(cr[i][j][r], ci[i][j][r]);
           }
       }
       zero();
@@ -467,58 +526,89 @@ __global__ void __launch_bounds__(kThreads, OAA_WAVES_GEMM) cgemm_mfma_kernel(Ge
   }
 }
 
-// Workgroups per CU and CU count of the current device for one kernel
-// instantiation, queried once per device.
-template <class Kern>
-hipError_t resident_groups(Kern kern, unsigned& groups) {
-  static int cached[64] = {0};
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-  if (cached[dev] == 0) {
-    int cus = 0, per_cu = 0;
-    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return e;
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kThreads, 0);
-    if (e != hipSuccess) return e;
-    cached[dev] = (per_cu < 1 ? 1 : per_cu) * (cus < 1 ? 1 : cus);
-  }
-  groups = unsigned(cached[dev]);
-  return hipSuccess;
-}
-
-template <int MB, int NB, bool AT, bool AC, bool BT, bool BC>
+template <int WM, int WN, int MB, int NB, bool AT, bool AC, bool BT>
 hipError_t launch_mfma_shape(const GemmParams& p, hipStream_t s) {
-  const unsigned long long tiles = (unsigned long long)((p.M + 32 * MB - 1) / (32 * MB)) *
-                                   ((p.N + 32 * NB - 1) / (32 * NB)) * unsigned(p.nsplit) * unsigned(p.F);
+  constexpr int TM = 16 * WM * MB, TN = 16 * WN * NB, threads = 64 * WM * WN;
+  constexpr size_t lds = mfma_lds_bytes(TM, TN);
+  const unsigned long long tiles = (unsigned long long)((p.M + TM - 1) / TM) * ((p.N + TN - 1) / TN) *
+                                   unsigned(p.nsplit) * unsigned(p.F);
   if (tiles == 0) return hipSuccess;
   if (tiles > 0xffffffffull) return hipErrorInvalidValue;
-  auto kern = cgemm_mfma_kernel<MB, NB, AT, AC, BT, BC>;
-  unsigned groups = 0;
-  hipError_t e = resident_groups(kern, groups);
+  auto kern = cgemm_mfma_kernel<WM, WN, MB, NB, AT, AC, BT>;
+  hipError_t e = lds > 65536 ? tile::allow_lds(kern, lds) : hipSuccess;
   if (e != hipSuccess) return e;
-  unsigned long long nwg = groups < tiles ? groups : tiles;
+  // resident workgroups of this instantiation, queried once per device
+  static std::atomic<int> resident[64];
+  int dev = 0;
+  if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
+  if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+  int groups = resident[dev].load(std::memory_order_relaxed);
+  if (groups == 0) {
+    int cus = 0, per_cu = 0;
+    if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
+    if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, threads, lds)) != hipSuccess) return e;
+    groups = (per_cu < 1 ? 1 : per_cu) * (cus < 1 ? 1 : cus);
+    resident[dev].store(groups, std::memory_order_relaxed);
+  }
+  unsigned long long nwg = (unsigned long long)(groups) < tiles ? groups : tiles;
   nwg = (nwg + 7) / 8 * 8;  // whole rounds over the 8 XCDs
-  hipLaunchKernelGGL(kern, dim3(unsigned(nwg)), dim3(kThreads), 0, s, p, unsigned(tiles));
+  hipLaunchKernelGGL(kern, dim3(unsigned(nwg)), dim3(threads), lds, s, p, unsigned(tiles));
   return hipGetLastError();
 }
 
-// Row tile of 96 when that wastes less than 128 does (e.g. 96 channels).
-// Where the rows are a multiple of 64 and 96-wide column tiles waste less
-// than 64-wide ones, 64 x 96 tiles (e.g. the large-kernel layer's forward
-// product: 288 tiles per bin, the fifth 64-wide column tile half empty;
-// 0.89 -> 0.86 ms). A 96 x 96 tile would need more than the 256 registers
-// of two workgroups per CU.
-template <bool AT, bool AC, bool BT, bool BC>
+// Estimated time (ns) of a contraction on TM x TN tiles: a CU's time for one
+// tile (matrix products of its slices; the split of the operands, 11 vector
+// instructions per element; a barrier per slice; the result stores), times the
+// tiles per CU, or once where there are fewer tiles than CUs. A 512-lane
+// workgroup has its CU to itself, so its rounds are whole ones. The rates are
+// a fixed calibration against sweeps over the tile shapes: the large-kernel
+// layer, 128 channels at 56 x 56, and layers of 5 to 138 channels. Within it
+// the shapes rank as they measured, e.g. 48 x 64 x 64 over 514 bins: 64 x 64
+// tiles 12 us (estimated 12), 32 x 64 13 (15), 96 x 64 18 (17), 32 x 32 17
+// (21); 256 x 288 x 96 over 2050 bins: 128 x 96 0.78 ms, 128 x 64 0.81,
+// 96 x 96 0.82, 128 x 128 0.85, 64 x 64 1.03.
+inline double mfma_estimate(const GemmParams& p, int TM, int TN, int threads) {
+  const double tiles = double((p.M + TM - 1) / TM) * ((p.N + TN - 1) / TN) * p.nsplit * p.F;
+  const double slices = (std::min(p.Kr, p.kchunk) + kKC - 1) / kKC;
+  const double area = double(TM) * TN;
+  const double tile = slices * (0.149 * area + 1.3 * (TM + TN) + 250) + 0.4 * area + 300;
+  const double rounds = threads > kThreads ? std::ceil(tiles / 256) : tiles / 256;
+  return std::max(1.0, rounds) * tile;
+}
+
+// The tile shape with the least estimated time.
+template <bool AT, bool AC, bool BT>
 hipError_t launch_mfma(const GemmParams& p, hipStream_t s) {
-  const long waste128 = (long)((p.M + 127) / 128) * 128 - p.M;
-  const long waste96 = (long)((p.M + 95) / 96) * 96 - p.M;
-  const long wasteN64 = (long)((p.N + 63) / 64) * 64 - p.N;
-  const long wasteN96 = (long)((p.N + 95) / 96) * 96 - p.N;
-  if (p.M % 64 == 0 && wasteN96 < wasteN64) return launch_mfma_shape<2, 3, AT, AC, BT, BC>(p, s);
-  if (waste96 < waste128) return launch_mfma_shape<3, OAA_GEMM_NB, AT, AC, BT, BC>(p, s);
-  return launch_mfma_shape<4, OAA_GEMM_NB, AT, AC, BT, BC>(p, s);
+  struct Shape {
+    int tm, tn, threads;
+    hipError_t (*launch)(const GemmParams&, hipStream_t);
+  };
+  static constexpr Shape kShapes[] = {
+      {16, 64, 256, launch_mfma_shape<1, 4, 1, 1, AT, AC, BT>},
+      {16, 128, 256, launch_mfma_shape<1, 4, 1, 2, AT, AC, BT>},
+      {64, 16, 256, launch_mfma_shape<4, 1, 1, 1, AT, AC, BT>},
+      {32, 32, 256, launch_mfma_shape<2, 2, 1, 1, AT, AC, BT>},
+      {32, 64, 256, launch_mfma_shape<2, 2, 1, 2, AT, AC, BT>},
+      {64, 32, 256, launch_mfma_shape<2, 2, 2, 1, AT, AC, BT>},
+      {64, 64, 256, launch_mfma_shape<2, 2, 2, 2, AT, AC, BT>},
+      {96, 64, 256, launch_mfma_shape<2, 2, 3, 2, AT, AC, BT>},
+      {64, 96, 256, launch_mfma_shape<2, 2, 2, 3, AT, AC, BT>},
+      {128, 64, 256, launch_mfma_shape<2, 2, 4, 2, AT, AC, BT>},
+      {96, 96, 256, launch_mfma_shape<2, 2, 3, 3, AT, AC, BT>},
+      {128, 96, 512, launch_mfma_shape<4, 2, 2, 3, AT, AC, BT>},
+      {96, 128, 512, launch_mfma_shape<2, 4, 3, 2, AT, AC, BT>},
+      {128, 128, 512, launch_mfma_shape<2, 4, 4, 2, AT, AC, BT>},
+  };
+  const Shape* best = nullptr;
+  double least = 0;
+  for (const Shape& sh : kShapes) {
+    const double t = mfma_estimate(p, sh.tm, sh.tn, sh.threads);
+    if (!best || t < least) {
+      best = &sh;
+      least = t;
+    }
+  }
+  return best->launch(p, s);
 }
 
 template <int TM, int TN, class Kern>
@@ -548,19 +638,21 @@ hipError_t launch_cgemm_valu(const GemmParams& p, hipStream_t s) {
 hipError_t launch_cgemm_mfma(const GemmParams& p, hipStream_t s) {
   if (p.kchunk % kKC != 0 && p.nsplit > 1) return hipErrorInvalidValue;
   if (!mfma_fits(p)) return hipErrorInvalidValue;
-  if (p.a_trans && !p.a_conj && !p.b_trans && !p.b_conj) return launch_mfma<true, false, false, false>(p, s);
-  if (!p.a_trans && p.a_conj && !p.b_trans && !p.b_conj) return launch_mfma<false, true, false, false>(p, s);
-  if (!p.a_trans && p.a_conj && p.b_trans && !p.b_conj) return launch_mfma<false, true, true, false>(p, s);
-  if (!p.a_trans && !p.a_conj && !p.b_trans && !p.b_conj) return launch_mfma<false, false, false, false>(p, s);
+  if (p.a_trans && !p.a_conj && !p.b_trans && !p.b_conj) return launch_mfma<true, false, false>(p, s);
+  if (!p.a_trans && p.a_conj && !p.b_trans && !p.b_conj) return launch_mfma<false, true, false>(p, s);
+  if (!p.a_trans && p.a_conj && p.b_trans && !p.b_conj) return launch_mfma<false, true, true>(p, s);
+  if (!p.a_trans && !p.a_conj && !p.b_trans && !p.b_conj) return launch_mfma<false, false, false>(p, s);
   return hipErrorInvalidValue;
 }
 
-// The matrix-core path reads each bin's operands through 32-bit byte offsets.
+// The matrix-core path reads each bin's operands through 32-bit byte offsets;
+// where the rows are contiguous, offsets of up to 16 reduction indices, also
+// of those past a short reduction, must not wrap.
 bool mfma_fits(const GemmParams& p) {
   const size_t lim = size_t(1) << 28;
-  return p.a_fstride < lim && p.b_fstride < lim && p.c_fstride < lim && size_t(p.M) * size_t(p.ldc) < lim;
+  const long row_lim = 1l << 25;
+  return p.a_fstride < lim && p.b_fstride < lim && p.c_fstride < lim && size_t(p.M) * size_t(p.ldc) < lim &&
+         (!p.a_trans || p.lda < row_lim) && (p.b_trans || p.ldb < row_lim);
 }
-
-bool mfma_preferred(const GemmParams& p) { return p.M >= 32 && p.N >= 32 && p.Kr >= 16 && mfma_fits(p); }
 
 }  // namespace oaa

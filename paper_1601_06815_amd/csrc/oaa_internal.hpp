@@ -226,10 +226,9 @@ hipError_t launch_cgemm_mfma(const GemmParams& p, hipStream_t s);
 constexpr int kNarrowMaxC = 4;
 hipError_t launch_cgemm_narrow(const GemmParams& p, hipStream_t s);
 bool narrow_supported(const GemmParams& p);
-// Shape rule of the automatic choice between the tiled contractions.
-bool mfma_preferred(const GemmParams& p);
 // Whether the matrix-core engine can address its operands and result with
-// 32-bit offsets (each bin's matrices under 2^28 complex elements).
+// 32-bit offsets (each bin's matrices under 2^28 complex elements); the
+// automatic choice takes it wherever it can and C > kNarrowMaxC.
 bool mfma_fits(const GemmParams& p);
 
 }  // namespace oaa

@@ -316,7 +316,7 @@ oaa_status_t kernel_chain(const Ctx& cx, const float* w1, int J, int n1, const f
   g.L = p->L;
   g.a_trans = false; g.a_conj = false; g.b_trans = false; g.b_conj = false;
   oaa_status_t st = timed(cx, OAA_STAGE_W_SPECTRUM, "kernel spectra of two stacked layers", [&] {
-    return oaa::mfma_preferred(g) ? oaa::launch_cgemm_mfma(g, cx.s) : oaa::launch_cgemm_valu(g, cx.s);
+    return oaa::mfma_fits(g) ? oaa::launch_cgemm_mfma(g, cx.s) : oaa::launch_cgemm_valu(g, cx.s);
   });
   if (st == OAA_OK && cx.own) p->w_valid = true;
   return st;
@@ -464,9 +464,9 @@ oaa_status_t run_gemm(const Ctx& cx, oaa::GemmParams& g, oaa_stage_t stage, cons
   g.L = p->L;
   oaa_contraction_t c = p->contraction;
   if (c == OAA_CONTRACTION_AUTO)
-    c = oaa::mfma_preferred(g)      ? OAA_CONTRACTION_MFMA
-        : oaa::narrow_supported(g) ? OAA_CONTRACTION_NARROW
-                                   : OAA_CONTRACTION_VALU;
+    c = oaa::narrow_supported(g) ? OAA_CONTRACTION_NARROW
+        : oaa::mfma_fits(g)      ? OAA_CONTRACTION_MFMA
+                                 : OAA_CONTRACTION_VALU;
   if (c == OAA_CONTRACTION_NARROW && !oaa::narrow_supported(g))
     return fail(OAA_ERR_UNSUPPORTED, "%s: the streaming contraction needs C <= %d", what, oaa::kNarrowMaxC);
   return timed(cx, stage, what, [&] {

@@ -99,6 +99,30 @@ def test_matrix_core_tile_shapes(gpu_lib, shape):
     check_whole(x, w, g, binding.CONTRACTION_MFMA, tiling=(L, b))
 
 
+@pytest.mark.parametrize("shape", [
+    (2, 5, 9, 20, 3, 16, 14),       # one slice or less of every reduction: 32 x 32 tiles
+    (5, 19, 27, 61, 9, 32, 24),     # odd sizes, ragged reductions: 32 x 64, 32 x 32
+    (3, 6, 40, 60, 5, 16, 12),      # few rows: 64 x 32, 16 x 64
+    (8, 5, 7, 60, 3, 16, 14),       # 16 x 128, split reduction
+    (30, 7, 150, 20, 3, 8, 6),      # 96 x 96, 16 x 64, 16 x 128
+    (30, 150, 7, 20, 3, 8, 6),      # 64 x 16
+    (8, 100, 200, 30, 3, 16, 14),   # 64 x 96, 128 x 64
+    (40, 96, 96, 30, 3, 16, 14),    # 96 x 96 in all three passes
+], ids=lambda s: "x".join(map(str, s)))
+def test_matrix_core_split(gpu_lib, shape):
+    """The contraction on three bf16 pieces per value, over its tile shapes,
+    against the oracle; and scaling an input by a power of two scales the
+    results exactly, as it does every fp32 step of the path (the pieces have
+    fp32's exponent range)."""
+    B, C, K, N, n, L, b = shape
+    x, w, g = make_inputs(Layer("t", B, C, K, N, n), seed=37 + sum(shape))
+    check_whole(x, w, g, tiling=(L, b))
+    _, y, dx, dw = run_layer(x, w, g, tiling=(L, b))
+    up = np.float32(2.0 ** 60)
+    _, y2, dx2, dw2 = run_layer(x * up, w, g / up, tiling=(L, b))
+    assert np.array_equal(y2, y * up) and np.array_equal(dx2, dx / up) and np.array_equal(dw2, dw)
+
+
 NARROW = [  # C <= 4: odd and even tile counts, K off multiples of 16, K > 64, K > 256, split reduction
     (1, 1, 1, 9, 3),
     (2, 2, 17, 13, 4),
