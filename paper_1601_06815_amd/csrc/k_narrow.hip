@@ -17,11 +17,12 @@
 // partial sums of the chunks are added by the inverse-transform kernel, in a
 // fixed order.
 //
-// With few tiles per bin (B P <= 64, e.g. the single images of the paper's
-// sweeps) a lane per tile would leave the workgroup nearly idle and walk all K
-// kernels in one dependent chain; the forward and backward_data variants for
-// that case spread the kernels over the lanes as well (one workgroup per bin),
-// and the backward_filter variant (B P <= 16) gives each lane one kernel.
+// With few tiles per bin (e.g. the single images of the paper's sweeps) a lane
+// per tile would leave the workgroup nearly idle and walk all K kernels in one
+// dependent chain. The variants for that case spread the kernels over the
+// lanes as well: forward, lanes over the bin's contiguous K x B P results;
+// backward_data, lanes over tiles and kernels, added in LDS; backward_filter
+// (B P <= 16), a lane per kernel.
 #include <algorithm>
 
 #include "oaa_internal.hpp"
@@ -37,7 +38,11 @@ constexpr int kThreads = 256;
 constexpr int kKB = 256;       // kernel spectra staged per LDS block
 constexpr int kIter = 4;       // groups of VEC tiles per lane (forward, backward_data)
 constexpr int kKG = 16;        // kernels per wave (backward_filter)
-constexpr int kFewTiles = 64;  // B P up to which the few-tile variants run
+// B P below which the few-tile variants of forward and backward_data run: the
+// others give a workgroup 2048 tiles (or 1024 where rows are not even).
+constexpr int kFewTiles = 1024;
+constexpr int kFewPerLane = 8;     // results per lane of the forward variant (many results)
+constexpr int kFewThreads = 1024;  // most lanes of the backward_data variant
 
 __device__ __forceinline__ float2 cmad_conj(float2 a, float2 b, float2 c) {
   // c + conj(a) * b
@@ -249,46 +254,80 @@ __global__ void __launch_bounds__(kThreads) narrow_bwd_filter_kernel(GemmParams 
   }
 }
 
-// Few tiles per bin: lane t takes tile j = t mod NB (NB = 2^nb_log2 >= B P)
-// and kernels t / NB + i 256 / NB. Forward: each lane writes its own outputs.
-template <int CN>
-__global__ void __launch_bounds__(kThreads) narrow_forward_few_kernel(GemmParams p, int nb_log2) {
-  const int f = unique_bin(blockIdx.x, p.L);
-  const int K = p.M, BP = p.N;
-  const int j = threadIdx.x & ((1 << nb_log2) - 1), nk = kThreads >> nb_log2;
-  if (j >= BP) return;  // no barrier below
+// Few tiles per bin, forward: the bin's results are one contiguous block of
+// K x B P, which the lanes walk in order in units of VEC neighbouring tiles,
+// so that every store is coalesced whatever B P is. 2^nl_log2 lanes take a
+// bin (grid.y ranges of it where it has more results than they hold). One
+// workgroup per bin with a lane per (kernel, tile) wrote 25 MB over 130 bins
+// (500 kernels, 49 tiles) in 26 us; this takes 10.
+template <int CN, int VEC, int PER>
+__global__ void __launch_bounds__(kThreads) narrow_forward_few_kernel(GemmParams p, int nl_log2) {
+  const unsigned fp = (blockIdx.x << (8 - nl_log2)) + (threadIdx.x >> nl_log2);
+  if (fp >= unsigned(p.F)) return;  // no barrier below
+  const int f = unique_bin(int(fp), p.L);
+  const unsigned nl = 1u << nl_log2, K = p.M, BP = unsigned(p.N) / VEC, total = K * BP;
   const float2* A = p.A + size_t(f) * p.a_fstride;
   const float2* B = p.B + size_t(f) * p.b_fstride;
   float2* O = p.C + size_t(f) * p.c_fstride;
-  float2 x[CN];
+  const unsigned i0 = blockIdx.y * (nl * PER) + (threadIdx.x & (nl - 1));
+  unsigned k = i0 / BP, j = i0 - k * BP;
+  const unsigned dk = nl / BP, dj = nl - dk * BP;
+  float2 w[PER][CN], x[PER][CN][VEC];
 #pragma unroll
-  for (int c = 0; c < CN; ++c) x[c] = B[c * p.ldb + j];
-#pragma unroll 4
-  for (int k = threadIdx.x >> nb_log2; k < K; k += nk) {
-    float2 y = make_float2(0.f, 0.f);
+  for (int it = 0; it < PER; ++it) {
+    const unsigned kc = min(k, K - 1);  // past the end: a valid address, not stored
 #pragma unroll
-    for (int c = 0; c < CN; ++c) y = cmad(y, A[c * p.lda + k], x[c]);
-    O[size_t(k) * p.ldc + j] = y;
+    for (int c = 0; c < CN; ++c) {
+      w[it][c] = A[c * p.lda + kc];
+      load_vec<VEC>(B + c * p.ldb + j * VEC, x[it][c]);
+    }
+    k += dk;
+    j += dj;
+    if (j >= BP) {
+      j -= BP;
+      ++k;
+    }
+  }
+#pragma unroll
+  for (int it = 0; it < PER; ++it) {
+    float2 y[VEC];
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) {
+      y[v] = make_float2(0.f, 0.f);
+#pragma unroll
+      for (int c = 0; c < CN; ++c) y[v] = cmad(y[v], w[it][c], x[it][c][v]);
+    }
+    const unsigned i = i0 + it * nl;
+    if (i < total) store_vec<VEC>(O + size_t(i) * VEC, y);
   }
 }
 
-// Few tiles per bin, backward_data: each lane sums its kernels for its tile,
-// then the 256 / NB lanes of a tile are added in LDS in a fixed order.
+// Few tiles per bin, backward_data: 2^nb_log2 * 2^nk_log2 lanes take a bin's
+// 2^nb_log2 tiles (grid.y ranges of them) and kernels kk + i 2^nk_log2 each;
+// the lanes of a tile are added in LDS in a fixed order. With one 256-lane
+// workgroup per bin, the 130 bins of a 16-point layer (500 kernels, 49 tiles)
+// had 2 waves per CU in flight and took 16 us, now 11; single tiles of
+// 128 points (100 kernels), whose last sum ran over 256 lanes, 20 us, now 5.5.
 template <int CN>
-__global__ void __launch_bounds__(kThreads) narrow_bwd_data_few_kernel(GemmParams p, int nb_log2) {
-  __shared__ float2 red[CN][kThreads];
-  const int f = unique_bin(blockIdx.x, p.L);
+__global__ void __launch_bounds__(kFewThreads) narrow_bwd_data_few_kernel(GemmParams p, int nb_log2, int nk_log2) {
+  __shared__ float2 red[CN][kFewThreads];
+  const int t = threadIdx.x, lane = t & ((1 << (nb_log2 + nk_log2)) - 1);  // within the bin's lanes
+  const unsigned per_wg = blockDim.x >> (nb_log2 + nk_log2);
+  const unsigned fp = blockIdx.x * per_wg + (unsigned(t) >> (nb_log2 + nk_log2));
+  const bool live = fp < unsigned(p.F);
+  const int f = unique_bin(int(live ? fp : 0), p.L);
   const int K = p.Kr, BP = p.N;
-  const int t = threadIdx.x, mask = (1 << nb_log2) - 1, j = t & mask, nk = kThreads >> nb_log2;
+  const int mask = (1 << nb_log2) - 1, nk = 1 << nk_log2;
+  const int j = (int(blockIdx.y) << nb_log2) + (lane & mask);
   const float2* A = p.A + size_t(f) * p.a_fstride;
   const float2* B = p.B + size_t(f) * p.b_fstride;
   float2* O = p.C + size_t(f) * p.c_fstride;
   float2 acc[CN];
 #pragma unroll
   for (int c = 0; c < CN; ++c) acc[c] = make_float2(0.f, 0.f);
-  if (j < BP) {
-#pragma unroll 4
-    for (int k = t >> nb_log2; k < K; k += nk) {
+  if (live && j < BP) {
+#pragma unroll 8
+    for (int k = lane >> nb_log2; k < K; k += nk) {
       const float2 g = B[size_t(k) * p.ldb + j];
 #pragma unroll
       for (int c = 0; c < CN; ++c) acc[c] = cmad_conj(A[c * p.lda + k], g, acc[c]);
@@ -297,15 +336,17 @@ __global__ void __launch_bounds__(kThreads) narrow_bwd_data_few_kernel(GemmParam
 #pragma unroll
   for (int c = 0; c < CN; ++c) red[c][t] = acc[c];
   __syncthreads();
-  if (t < (CN << nb_log2) && (t & mask) < BP) {
-    const int c = t >> nb_log2, jj = t & mask;
-    float2 sum = make_float2(0.f, 0.f);
-    for (int q = 0; q < nk; ++q) {
-      const float2 v = red[c][(q << nb_log2) + jj];
-      sum.x += v.x;
-      sum.y += v.y;
+  if (live && lane <= mask && j < BP) {
+#pragma unroll
+    for (int c = 0; c < CN; ++c) {
+      float2 sum = make_float2(0.f, 0.f);
+      for (int q = 0; q < nk; ++q) {
+        const float2 v = red[c][t + (q << nb_log2)];
+        sum.x += v.x;
+        sum.y += v.y;
+      }
+      O[c * p.ldc + j] = sum;
     }
-    O[c * p.ldc + jj] = sum;
   }
 }
 
@@ -334,10 +375,43 @@ __global__ void __launch_bounds__(kThreads) narrow_bwd_filter_few_kernel(GemmPar
   for (int c = 0; c < CN; ++c) out[size_t(c) * p.ldc + k] = acc[c];
 }
 
-int few_tiles_log2(long BP) {
+int log2_at_least(long v, int most) {
   int l = 0;
-  while ((1L << l) < BP) ++l;
+  while (l < most && (1L << l) < v) ++l;
   return l;
+}
+
+template <int CN, int VEC, int PER>
+hipError_t launch_fwd_few_per(const GemmParams& p, hipStream_t s) {
+  const unsigned total = unsigned(p.M) * unsigned(p.N) / VEC;
+  const int nl = std::max(6, log2_at_least((total + PER - 1) / PER, 8));
+  const unsigned bins = kThreads >> nl, per = (1u << nl) * PER;
+  hipLaunchKernelGGL((narrow_forward_few_kernel<CN, VEC, PER>),
+                     dim3((unsigned(p.F) + bins - 1) / bins, (total + per - 1) / per), dim3(kThreads), 0, s, p, nl);
+  return hipGetLastError();
+}
+
+// Eight results per lane, or one where that leaves fewer than two workgroups
+// per CU (4 kernels on 49 tiles of 16 points: 4.3 against 2.6 us).
+template <int CN, int VEC>
+hipError_t launch_fwd_few(const GemmParams& p, hipStream_t s) {
+  const double wgs = double(p.F) * p.M * p.N / VEC / (kThreads * kFewPerLane);
+  return wgs >= 512 ? launch_fwd_few_per<CN, VEC, kFewPerLane>(p, s) : launch_fwd_few_per<CN, VEC, 1>(p, s);
+}
+
+template <int CN>
+hipError_t launch_bwd_data_few(const GemmParams& p, hipStream_t s) {
+  // tiles on up to 256 lanes; eight kernels per lane (two where there are few
+  // values in all), up to 1024 lanes per bin, bins of fewer than 256 lanes
+  // together in a workgroup
+  const int per = double(p.F) * p.N * p.Kr < (1 << 18) ? 2 : 8;
+  const int nb = log2_at_least(p.N, 8), nk = log2_at_least((p.Kr + per - 1) / per, 10 - nb);
+  const int threads = std::max(256, 1 << (nb + nk));
+  const unsigned bins = unsigned(threads) >> (nb + nk);
+  hipLaunchKernelGGL(narrow_bwd_data_few_kernel<CN>,
+                     dim3((unsigned(p.F) + bins - 1) / bins, unsigned((p.N + (1 << nb) - 1) >> nb)), dim3(threads), 0,
+                     s, p, nb, nk);
+  return hipGetLastError();
 }
 
 template <int CN, int VEC>
@@ -370,17 +444,11 @@ bool pairs_ok(long ld, long chunk, int nsplit) { return ld % 2 == 0 && (nsplit =
 
 template <int CN>
 hipError_t launch_narrow_c(const GemmParams& p, hipStream_t s) {
-  const bool few = p.N >= 1 && p.N <= kFewTiles && p.nsplit == 1;
-  if (few && p.a_trans && !p.a_conj && !p.b_trans && !p.b_conj) {
-    hipLaunchKernelGGL(narrow_forward_few_kernel<CN>, dim3(unsigned(p.F)), dim3(kThreads), 0, s, p,
-                       few_tiles_log2(p.N));
-    return hipGetLastError();
-  }
-  if (few && !p.a_trans && p.a_conj && !p.b_trans && !p.b_conj) {
-    hipLaunchKernelGGL(narrow_bwd_data_few_kernel<CN>, dim3(unsigned(p.F)), dim3(kThreads), 0, s, p,
-                       few_tiles_log2(p.N));
-    return hipGetLastError();
-  }
+  const bool few = p.N >= 1 && p.N < kFewTiles && p.nsplit == 1;
+  if (few && p.a_trans && !p.a_conj && !p.b_trans && !p.b_conj && p.ldc == p.N &&
+      (unsigned long long)p.M * p.N < (1ull << 26))
+    return p.N % 2 == 0 ? launch_fwd_few<CN, 2>(p, s) : launch_fwd_few<CN, 1>(p, s);
+  if (few && !p.a_trans && p.a_conj && !p.b_trans && !p.b_conj) return launch_bwd_data_few<CN>(p, s);
   if (p.Kr >= 1 && p.Kr <= kFewTilesFilter && p.nsplit == 1 && !p.a_trans && p.a_conj && p.b_trans && !p.b_conj) {
     hipLaunchKernelGGL(narrow_bwd_filter_few_kernel<CN>, dim3(unsigned((p.N + kThreads - 1) / kThreads), unsigned(p.F)),
                        dim3(kThreads), 0, s, p);

@@ -133,6 +133,22 @@ NARROW = [  # C <= 4: odd and even tile counts, K off multiples of 16, K > 64, K
 ]
 
 
+@pytest.mark.parametrize("shape", [
+    (1, 1, 1, 20, 12, 32, 20),     # one tile, one kernel
+    (1, 1, 100, 40, 20, 64, 45),   # one tile, kernels over lanes: several bins per workgroup
+    (1, 2, 33, 60, 5, 16, 12),     # 25 tiles (odd: single results), two results of one lane in different rows
+    (1, 3, 500, 48, 5, 16, 12),    # 16 tiles, many kernels: pairs of results, ranges of a bin
+    (3, 4, 9, 100, 5, 16, 12),     # 243 tiles
+    (2, 1, 40, 130, 5, 16, 8),     # 578 tiles: ranges of tiles in the error propagation
+    (4, 1, 3, 130, 3, 8, 6),       # 1936 tiles: past the few-tile kernels
+], ids=lambda s: "x".join(map(str, s)))
+def test_few_tiles_per_bin(gpu_lib, shape):
+    """The streaming contraction's few-tile kernels over their lane layouts."""
+    B, C, K, N, n, L, b = shape
+    x, w, g = make_inputs(Layer("t", B, C, K, N, n), seed=41 + sum(shape))
+    check_whole(x, w, g, binding.CONTRACTION_NARROW, tiling=(L, b))
+
+
 @pytest.mark.parametrize("shape", NARROW, ids=lambda s: "x".join(map(str, s)))
 def test_narrow_contraction(gpu_lib, shape):
     """The streaming contraction for few input channels, forced, against the
