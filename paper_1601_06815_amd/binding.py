@@ -224,6 +224,12 @@ class Plan:
         self.geometry = oaa_plan_geometry(self.handle)
         self.device = torch.device(device)
         self.generation = 0
+        self._torch = torch
+        # shapes of the passes' tensors
+        g = self.geometry
+        self._x = torch.Size((g["B"], g["C"], g["N"], g["N"]))
+        self._w = torch.Size((g["K"], g["C"], g["n"], g["n"]))
+        self._y = torch.Size((g["B"], g["K"], g["M"], g["M"]))
         nbytes = oaa_plan_workspace_bytes(self.handle)
         self.workspace = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=self.device)
         self._streams = {torch.cuda.current_stream(self.device).cuda_stream}
@@ -252,60 +258,54 @@ class Plan:
         return not self.geometry["fused"]
 
     def _ptr(self, t, shape, name):
-        import torch
         if t is None:
             return None
-        if t.dtype != torch.float32 or not t.is_contiguous() or t.device != self.device:
+        if t.dtype != self._torch.float32 or not t.is_contiguous() or t.device != self.device:
             raise ValueError(f"{name} must be a contiguous float32 tensor on {self.device}")
-        if tuple(t.shape) != tuple(shape):
+        if t.shape != shape:
             raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
         return t.data_ptr()
 
     def _stream(self):
-        import torch
-        s = torch.cuda.current_stream(self.device)
-        if s.cuda_stream not in self._streams:
+        # the raw handle: a Stream object costs several times as much, most of
+        # all in autograd's backward thread
+        index = self.device.index
+        raw = self._torch._C._cuda_getCurrentRawStream(
+            self._torch.cuda.current_device() if index is None else index)
+        if raw not in self._streams:
+            s = self._torch.cuda.current_stream(self.device)
             self.workspace.record_stream(s)
-            self._streams.add(s.cuda_stream)
-        return s.cuda_stream
+            self._streams.add(raw)
+        return raw
 
     def _empty(self, shape):
-        import torch
-        return torch.empty(shape, dtype=torch.float32, device=self.device)
+        return self._torch.empty(shape, dtype=self._torch.float32, device=self.device)
 
     def forward(self, x, w, y=None):
-        g = self.geometry
-        B, C, K, N, n, M = g["B"], g["C"], g["K"], g["N"], g["n"], g["M"]
-        y = self._empty((B, K, M, M)) if y is None else y
-        oaa_conv_forward(self.handle, self._ptr(x, (B, C, N, N), "x"), self._ptr(w, (K, C, n, n), "w"),
-                         self._ptr(y, (B, K, M, M), "y"), self._stream())
+        y = self._empty(self._y) if y is None else y
+        oaa_conv_forward(self.handle, self._ptr(x, self._x, "x"), self._ptr(w, self._w, "w"),
+                         self._ptr(y, self._y, "y"), self._stream())
         self.generation += 1
         return y
 
     def forward_noalloc(self, x, w, y):
         """oaa_conv_forward_noalloc into the caller's y: the library's static
         scratch instead of this plan's workspace, no allocation."""
-        g = self.geometry
-        B, C, K, N, n, M = g["B"], g["C"], g["K"], g["N"], g["n"], g["M"]
-        oaa_conv_forward_noalloc(self.handle, self._ptr(x, (B, C, N, N), "x"), self._ptr(w, (K, C, n, n), "w"),
-                                 self._ptr(y, (B, K, M, M), "y"), self._stream())
+        oaa_conv_forward_noalloc(self.handle, self._ptr(x, self._x, "x"), self._ptr(w, self._w, "w"),
+                                 self._ptr(y, self._y, "y"), self._stream())
         return y
 
     def backward_data(self, gr, w, dx=None):
-        g = self.geometry
-        B, C, K, N, n, M = g["B"], g["C"], g["K"], g["N"], g["n"], g["M"]
-        dx = self._empty((B, C, N, N)) if dx is None else dx
-        oaa_conv_backward_data(self.handle, self._ptr(gr, (B, K, M, M), "g"), self._ptr(w, (K, C, n, n), "w"),
-                               self._ptr(dx, (B, C, N, N), "dx"), self._stream())
+        dx = self._empty(self._x) if dx is None else dx
+        oaa_conv_backward_data(self.handle, self._ptr(gr, self._y, "g"), self._ptr(w, self._w, "w"),
+                               self._ptr(dx, self._x, "dx"), self._stream())
         self.generation += 1
         return dx
 
     def backward_filter(self, x, gr, dw=None):
-        g = self.geometry
-        B, C, K, N, n, M = g["B"], g["C"], g["K"], g["N"], g["n"], g["M"]
-        dw = self._empty((K, C, n, n)) if dw is None else dw
-        oaa_conv_backward_filter(self.handle, self._ptr(x, (B, C, N, N), "x"), self._ptr(gr, (B, K, M, M), "g"),
-                                 self._ptr(dw, (K, C, n, n), "dw"), self._stream())
+        dw = self._empty(self._w) if dw is None else dw
+        oaa_conv_backward_filter(self.handle, self._ptr(x, self._x, "x"), self._ptr(gr, self._y, "g"),
+                                 self._ptr(dw, self._w, "dw"), self._stream())
         self.generation += 1
         return dw
 
