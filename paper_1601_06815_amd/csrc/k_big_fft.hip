@@ -1,11 +1,13 @@
-// Transforms of side L = 64 and 128 (arXiv:1601.06815, Section 2: block
-// division, zero padding, the per-block transforms and the overlap-add of the
-// block results; Section 3.3 for the transform sides of large kernels), as
-// used for large blocks (b up to L - n + 1) and large kernels.
+// Transforms of side L = 64 (arXiv:1601.06815, Section 2: block division, zero
+// padding, the per-block transforms and the overlap-add of the block results;
+// Section 3.3 for the transform sides of large kernels), as used for large
+// blocks (b up to L - n + 1) and large kernels, in launches of many tiles; and
+// the launchers of both large sides, which give L = 128 and launches of few
+// tiles to k_wide_fft.hip.
 //
-// A workgroup keeps the intermediate of TQ tiles in LDS (17 KB per tile at
-// L = 64, so one workgroup of up to nine tiles per CU) and walks over groups
-// of TQ consecutive tiles of one channel:
+// A workgroup keeps the intermediate of TQ tiles in LDS (17 KB per tile, so
+// one workgroup of up to nine tiles per CU) and walks over groups of TQ
+// consecutive tiles of one channel:
 //  * forward: pass 1 transforms the column pairs (s, s + L/2) of every window
 //    along its rows, lanes over consecutive columns so that the loads of a
 //    row are coalesced, and keeps rows u <= L/2 of the two real columns'
@@ -17,18 +19,13 @@
 //    neighbouring groups write into a bin meet in that XCD's L2;
 //  * inverse: pass 1 inverts the columns v <= L/2 (loads in runs of TQ
 //    tiles), pass 2 inverts row pairs to real rows, pass 3 writes the kept
-//    part of each tile (crop) or the overlap-added plane. At L = 64 teams of
-//    workgroups of one XCD take neighbouring groups together, each team
-//    walking a contiguous range, so that the 128-byte lines that those
-//    groups' runs share come from HBM once; at L = 128 a workgroup walks a
-//    contiguous range of groups.
-// At L = 64 a lane holds a whole 64-point sequence, and the two halves of the
-// workgroup alternate between transforming a group and loading the next into
-// their registers (big_rfft2_lane_kernel, big_irfft2_lane_kernel). At
-// L = 128, and for forward launches of few groups, each L-point transform is
-// split over a pair of neighbouring lanes (fft_dif_split, L/2 complex values
-// per lane) and the whole workgroup transforms a group; the forward loads the
-// next group into registers while the current group's second pass runs.
+//    part of each tile (crop) or the overlap-added plane. Teams of workgroups
+//    of one XCD take neighbouring groups together, each team walking a
+//    contiguous range, so that the 128-byte lines that those groups' runs
+//    share come from HBM once.
+// A lane holds a whole 64-point sequence, and the two halves of the workgroup
+// alternate between transforming a group and loading the next into their
+// registers (big_rfft2_lane_kernel, big_irfft2_lane_kernel).
 #include <algorithm>
 #include <type_traits>
 
@@ -44,45 +41,24 @@ using namespace tile;
 
 constexpr size_t kBigLds = 160 * 1024;  // LDS of one CU
 
-// Tiles per group at L = 64 (overridable at build time for tuning sweeps).
+// Tiles per group (overridable at build time for tuning sweeps).
 #ifndef OAA_BIG_TQ
 #define OAA_BIG_TQ 8
 #endif
 
-template <int L>
 struct Big {
-  static constexpr int H2 = L / 2, V = L / 2 + 1;
+  static constexpr int L = 64, H2 = L / 2, V = L / 2 + 1;
   // forward LDS row stride (complex): columns [0, L/2) then, one slot on,
   // columns [L/2, L)
   static constexpr int RS = L + 2;
   // inverse LDS row stride (complex): L/2 slots, slot 0 holding the real
   // columns 0 and L/2 as (re, im), plus one slot of padding
   static constexpr int RI = H2 + 1;
-  static constexpr int TQ_MAX = L == 64 ? 9 : 2;  // tiles per group (LDS)
-  static constexpr int SIDE_MAX = L == 64 ? 3 : 1;  // blocks per side of a one-group plane
+  static constexpr int TQ_MAX = 9;    // tiles per group (LDS)
+  static constexpr int SIDE_MAX = 3;  // blocks per side of a one-group plane
 };
 
-// threads of a lane-pair forward workgroup: eight waves, which leaves a lane
-// 256 registers; L per tile, one task per thread with the register prefetch,
-// else threads loop over the tasks
-template <int L, bool PF>
-constexpr int big_threads() {
-  return 512;
-}
-// threads of an inverse workgroup: eight waves (a lane's registers capped
-// at 256)
-constexpr int kBigInvThreads = 512;
-
-// LDS per tile (complex elements, odd)
-template <int L>
-__host__ __device__ inline int fwd_tile_stride() {
-  return odd_at_least(Big<L>::H2 * Big<L>::RS);
-}
-template <int L>
-__host__ __device__ inline int inv_tile_stride(int KR) {
-  return odd_at_least(KR * Big<L>::RI);
-}
-// LDS per tile of the one-lane L = 64 kernels (complex elements): the 32 x 66
+// LDS per tile (complex elements): the 32 x 66
 // (forward) or 64 x 33 (inverse) slots, padded to 3 mod 32, so that tile
 // bases fall 6 four-byte banks apart. A wave's lanes over (tile, LDS row) in
 // the forward's second pass, and over (tile, column) or (tile, row pair) in
@@ -91,8 +67,8 @@ __host__ __device__ inline int inv_tile_stride(int KR) {
 // column (measured at the large-kernel layer: forward inverse 0.621 ->
 // 0.615 ms).
 __host__ __device__ constexpr int lane_tile_stride() {
-  constexpr int n = 64 * Big<64>::RI;
-  static_assert(n == 32 * Big<64>::RS, "both directions hold 2112 complex per tile");
+  constexpr int n = 64 * Big::RI;
+  static_assert(n == 32 * Big::RS, "both directions hold 2112 complex per tile");
   return n + ((3 - n % 32) + 32) % 32;
 }
 
@@ -103,23 +79,13 @@ __device__ __forceinline__ long first_group() {
   return long(blockIdx.x % 8) * (nwg / 8) + blockIdx.x / 8;
 }
 
-// The groups a workgroup takes: g, g + step, ... below end. Interleaved
-// (consecutive groups on the workgroups of one XCD at about the same time)
-// or, with `contig`, a contiguous range per workgroup (the workgroups of one
-// XCD holding consecutive ranges). The forward transforms walk interleaved;
-// the L = 128 inverse walks contiguous ranges (at L = 64 that was 0.99 ->
-// 0.93 ms against interleaved for the large-kernel forward inverse).
+// The groups a workgroup takes: g, g + step, ... below end. The forward
+// transform walks interleaved: consecutive groups on the workgroups of one
+// XCD at about the same time.
 struct GroupWalk {
   long g, end, step;
 };
-__device__ __forceinline__ GroupWalk group_walk(long ngroups, bool contig) {
-  const long w = first_group();
-  if (contig) {
-    const long nwg = gridDim.x, R = (ngroups + nwg - 1) / nwg;
-    return {w * R, min(ngroups, (w + 1) * R), 1};
-  }
-  return {w, ngroups, long(gridDim.x)};
-}
+__device__ __forceinline__ GroupWalk group_walk(long ngroups) { return {first_group(), ngroups, long(gridDim.x)}; }
 
 // Teams of S workgroups of one XCD (consecutive first_group numbers; nwg is
 // a multiple of 8 S, else S is 1) take S consecutive groups at a time, and
@@ -143,7 +109,8 @@ __device__ __forceinline__ GroupWalk group_walk_team(long ngroups, int S0) {
 }
 
 // ---------------------------------------------------------------------------
-// forward: windows of planes -> half spectra
+// forward: windows of planes -> half spectra, a whole 64-point sequence per
+// lane.
 //
 // Pass 1: z = x[., j] + i x[., j + L/2] along the rows; the real columns'
 // spectra are C_j[u] = (Z[u] + conj Z[-u]) / 2, C_{j+L/2}[u] =
@@ -152,147 +119,8 @@ __device__ __forceinline__ GroupWalk group_walk_team(long ngroups, int S0) {
 // [1, L/2) along the columns give bins (u, v), v <= L/2, and (L - u, v) =
 // conj X[u][L - v], 0 < v < L/2 (the other bins of rows past L/2 are
 // conjugates that nothing reads); the packed row gives rows 0 and L/2 by the
-// same separation as pass 1.
-template <int L, bool O32, bool PF>
-__global__ void __launch_bounds__((big_threads<L, PF>())) big_rfft2_kernel(BigFwdParams p) {
-  constexpr int H2 = Big<L>::H2, V = Big<L>::V, RS = Big<L>::RS;
-  static_assert(L >= 64, "the pass-1 lanes of one tile must fill whole waves");
-  extern __shared__ float smem[];
-  float2* lds = reinterpret_cast<float2*>(smem);
-  const int TSZ = fwd_tile_stride<L>();
-  const int tid = threadIdx.x, h = tid & 1;
-  const int P = p.T * p.T, tpc = p.n_img * P;
-  const size_t bs = p.bs;
-  const long ngroups = long(p.n_ch) * p.ngrp;
-  // pass 1: tile q1, columns j and j + L/2, rows [h L/2, h L/2 + L/2); a
-  // wave holds one tile (lane = h + 2 (j + (L/2) q1))
-  const int j = (tid >> 1) % H2, q1 = (tid >> 1) / H2;
-  // pass 2: tile q2 (fastest), LDS row u
-  const int q2 = (tid >> 1) % p.TQ, u = (tid >> 1) / p.TQ;
-  float zr[H2], zi[H2];
-
-  // part 0: columns j (zr), 1: columns j + L/2 (zi), 2: both
-  auto load = [&](long gg, int part) {
-    const int ch = int(gg / p.ngrp), t0 = int(gg % p.ngrp) * p.TQ;
-    const int nq = min(p.TQ, tpc - t0);
-    if (q1 >= nq) return;
-    const int t = t0 + q1, img = t / P, pp = t - img * P;
-    const int pr = pp / p.T, qc = pp - pr * p.T;
-    const float* plane = p.src + (size_t(img) * p.n_ch + ch) * size_t(p.H) * size_t(p.H);
-    const __amdgpu_buffer_rsrc_t rs = buffer_resource(plane, unsigned(p.H) * unsigned(p.H) * 4u);
-    const int gr0 = pr * p.pitch - p.off + h * H2;
-    const int ca = qc * p.pitch - p.off + j, cb = ca + H2;
-    const bool oka = j < p.S && unsigned(ca) < unsigned(p.H);
-    const bool okb = j + H2 < p.S && unsigned(cb) < unsigned(p.H);
-    const int lim = p.S - h * H2;  // rows of this half inside the window
-#pragma unroll
-    for (int i = 0; i < H2; ++i) {
-      const int gr = gr0 + i;
-      const bool okr = i < lim && unsigned(gr) < unsigned(p.H);
-      if (part != 1) zr[i] = buffer_load_f1(rs, okr && oka ? unsigned(gr * p.H + ca) * 4u : kOutOfRange);
-      if (part != 0) zi[i] = buffer_load_f1(rs, okr && okb ? unsigned(gr * p.H + cb) * 4u : kOutOfRange);
-    }
-  };
-
-  const GroupWalk wk = group_walk(ngroups, false);
-  long g = wk.g;
-  if (PF && g < wk.end) load(g, 2);
-  for (; g < wk.end; g += wk.step) {
-    const int ch = int(g / p.ngrp), t0 = int(g % p.ngrp) * p.TQ;
-    const int nq = min(p.TQ, tpc - t0);
-    if (!PF) load(g, 2);
-    if (q1 < nq) {
-      fft_dif_split<L, -1>(zr, zi, h);  // lane h: Z[2m + h] at bitrev(m)
-      float2* bq = lds + q1 * TSZ;
-#pragma unroll
-      for (int m = 1; m < H2 / 2; ++m) {  // u = 2m + h in [2, L/2), with u = 1 below
-        const int uu = 2 * m + h;
-        const int ps = bitrev(m, H2);
-        const int p0 = bitrev(H2 - m, H2), p1 = bitrev(H2 - m - 1, H2);  // -uu for h = 0, 1
-        const float a = zr[ps], b = zi[ps];
-        const float c = pick(h, zr[p1], zr[p0]), d = pick(h, zi[p1], zi[p0]);
-        bq[uu * RS + j] = make_float2(0.5f * (a + c), 0.5f * (b - d));
-        bq[uu * RS + H2 + 1 + j] = make_float2(0.5f * (b + d), 0.5f * (c - a));
-      }
-      // m = 0: u = 0 (lane 0) and u = 1 (lane 1, partner L - 1 at m = L/2 - 1);
-      // lane 0 also holds u = L/2 at m = L/4
-      const float a0 = zr[0], b0 = zi[0];
-      if (h) {
-        const int pl = bitrev(H2 - 1, H2);
-        const float c = zr[pl], d = zi[pl];
-        bq[RS + j] = make_float2(0.5f * (a0 + c), 0.5f * (b0 - d));
-        bq[RS + H2 + 1 + j] = make_float2(0.5f * (b0 + d), 0.5f * (c - a0));
-      } else {
-        const int ph = bitrev(H2 / 2, H2);
-        bq[j] = make_float2(a0, zr[ph]);
-        bq[H2 + 1 + j] = make_float2(b0, zi[ph]);
-      }
-    }
-    // The next group's windows load during pass 2, in two halves: a lane's
-    // 64 loads exceed the 63 vector memory instructions a wave can have in
-    // flight, and issued at once they stall the wave (and queue this pass's
-    // stores behind them). Half goes out before the barrier, half after it
-    // (measured at the large-kernel layer, gradient windows: all 64 after
-    // the barrier 0.69 ms, all before it 0.66 ms, split 0.56 ms).
-    const bool nxt = PF && g + wk.step < wk.end;
-    if (nxt) load(g + wk.step, 0);
-    __syncthreads();
-    if (nxt) load(g + wk.step, 1);
-    if (q2 < nq && u < H2) {
-      const float2* row = lds + q2 * TSZ + u * RS + h * (H2 + 1);
-      float re[H2], im[H2];
-#pragma unroll
-      for (int i = 0; i < H2; ++i) {
-        const float2 z = row[i];
-        re[i] = z.x;
-        im[i] = z.y;
-      }
-      fft_dif_split<L, -1>(re, im, h);  // lane h: Y[2m + h] at bitrev(m)
-      const int t = t0 + q2;
-      const size_t tb = size_t(ch) * p.cs + size_t(t / p.run) * p.rs + size_t(t % p.run);
-      // bins (r, v) for v = 2m + h: element (r V + h) bs + tb + m (2 bs)
-      auto put = [&](int r, int m, float2 val) {
-        if (O32) {
-          store_at(p.dst, unsigned(((size_t(r) * V + h) * bs + tb) * 8u) + unsigned(m) * unsigned(2 * bs * 8u), val);
-        } else {
-          p.dst[(size_t(r) * V + h) * bs + tb + size_t(2 * m) * bs] = val;
-        }
-      };
-      if (u > 0) {
-#pragma unroll
-        for (int m = 0; m <= H2 / 2; ++m) {
-          const int v = 2 * m + h, ps = bitrev(m, H2);
-          if (v <= H2) put(u, m, make_float2(re[ps], im[ps]));
-          if (v >= 1 && v < H2) {
-            const int q0i = bitrev((H2 - m) % H2, H2), q1i = bitrev(H2 - m - 1, H2);
-            const float xr = pick(h, re[q1i], re[q0i]), xi = pick(h, im[q1i], im[q0i]);
-            put(L - u, m, make_float2(xr, -xi));
-          }
-        }
-      } else {
-        // packed row: Y = X[0] + i X[L/2] (both Hermitian in v)
-#pragma unroll
-        for (int m = 0; m <= H2 / 2; ++m) {
-          const int v = 2 * m + h, ps = bitrev(m, H2);
-          if (v > H2) continue;
-          const int q0i = bitrev((H2 - m) % H2, H2), q1i = bitrev((H2 - m - 1 + H2) % H2, H2);
-          const float a = re[ps], b = im[ps];
-          const float c = pick(h, re[q1i], re[q0i]), d = pick(h, im[q1i], im[q0i]);
-          put(0, m, make_float2(0.5f * (a + c), 0.5f * (b - d)));
-          put(H2, m, make_float2(0.5f * (b + d), 0.5f * (c - a)));
-        }
-      }
-    }
-    __syncthreads();
-  }
-}
-
-// ---------------------------------------------------------------------------
-// forward at L = 64 with a whole 64-point sequence per lane: a lane
-// transforms one column pair (j, j + L/2) of a window along its rows (pass
-// 1), then one LDS row along the columns (pass 2). The separations, the LDS
-// layout and the bins written are those of the kernel above; without the
-// first stage across a lane pair a transform takes about 0.7 of the vector
+// same separation as pass 1. Against a transform split over a lane pair, with
+// its first stage across the pair, one lane takes about 0.7 of the vector
 // instructions. The 32 tasks per tile and pass of a group of eight tiles fill
 // four waves, half the workgroup, and the halves alternate: while one
 // transforms group i, the other loads the windows of group i + 1 into its
@@ -306,7 +134,7 @@ __global__ void __launch_bounds__((big_threads<L, PF>())) big_rfft2_kernel(BigFw
 // through 64-bit addresses.
 template <bool WIDE>
 __global__ void __launch_bounds__(512) big_rfft2_lane_kernel(BigFwdParams p) {
-  constexpr int L = 64, H2 = L / 2, V = L / 2 + 1, RS = Big<L>::RS;
+  constexpr int L = 64, H2 = L / 2, V = L / 2 + 1, RS = Big::RS;
   extern __shared__ float smem[];
   float2* lds = reinterpret_cast<float2*>(smem);
   const int TSZ = lane_tile_stride();
@@ -408,7 +236,7 @@ __global__ void __launch_bounds__(512) big_rfft2_lane_kernel(BigFwdParams p) {
     }
   };
 
-  const GroupWalk wk = group_walk(ngroups, false);
+  const GroupWalk wk = group_walk(ngroups);
   if (half == 0 && wk.g < wk.end) fetch(wk.g);
   int turn = 0;  // the half whose windows are in registers for this group
   for (long g = wk.g; g < wk.end; g += wk.step, turn ^= 1) {
@@ -433,20 +261,19 @@ __global__ void __launch_bounds__(512) big_rfft2_lane_kernel(BigFwdParams p) {
 // lane's column offsets in the (at most two) tiles covering its columns, with
 // 0/1 weights, are taken once per plane, so that the reads of a row need no
 // per-lane branch; the tile rows covering a row are the same for the whole
-// wave. RAW: rows and columns are at their inverse index r, kept index
-// (r + rot) mod L, and hold L^2 times the values; else at kept index, scaled.
-template <int L, bool RAW>
+// wave. Rows and columns are at their inverse index r, kept index
+// (r + rot) mod L, and hold L^2 times the values.
 __device__ __forceinline__ void overlap_plane_out(const BigInvParams& p, const float* ldf, int TSZ, int ch, int t0,
                                                   int wave, int lane, int nwave) {
-  constexpr int RI = Big<L>::RI;
+  constexpr int RI = Big::RI, L = 64;
   const int H = p.H, KR = p.KR, P = p.T * p.T;
   // stored index of kept index k
-  auto at = [&](int k) { return RAW ? (k - p.rot) & (L - 1) : k; };
-  const float wt = RAW ? 1.0f / float(L * L) : 1.0f;
+  auto at = [&](int k) { return (k - p.rot) & (L - 1); };
+  const float wt = 1.0f / float(L * L);
   const int img = t0 / P, T = p.T, b = p.pitch;
   float* out = p.dst + (size_t(img) * p.n_ch + ch) * H * H;
   const SmallDiv div_b(b);
-  constexpr int MCH = (L * Big<L>::SIDE_MAX + 63) / 64;  // H < T b <= L T
+  constexpr int MCH = (L * Big::SIDE_MAX + 63) / 64;  // H < T b <= L T
   int o0[MCH], o1[MCH];
   float m0[MCH], m1[MCH];
   int ln = lane;  // opaque: the offsets are not kept across the group loop
@@ -489,191 +316,13 @@ __device__ __forceinline__ void overlap_plane_out(const BigInvParams& p, const f
 
 // ---------------------------------------------------------------------------
 // inverse: half spectra -> kept part of every tile (crop), or the plane the
-// tiles overlap-add to
+// tiles overlap-add to, a whole 64-point sequence per lane.
 //
 // Pass 1 inverts column w of every tile, w < L/2; column 0 carries the real
 // columns 0 and L/2 together as h0[u] + i h1[u] (rows past L/2 rebuilt as the
 // conjugates of rows L - u, which are not stored), so its inverse holds both
-// real columns. Row r of the inverse becomes kept row (r + rot) mod L. Pass 2
-// inverts pairs of kept rows to real rows, written over their own storage;
-// column s becomes kept column (s + rot) mod L.
-// MODE: the kernel's pass 3 (0 crop, 1 overlap-add of one-group planes, 2
-// tiles to the scratch), fixed per instance so that each carries only the
-// registers of its own output code.
-template <int L, bool O32, int MODE>
-__global__ void __launch_bounds__(kBigInvThreads) big_irfft2_kernel(BigInvParams p) {
-  constexpr int H2 = Big<L>::H2, V = Big<L>::V, RI = Big<L>::RI;
-  extern __shared__ float smem[];
-  float2* lds = reinterpret_cast<float2*>(smem);
-  const float* ldf = smem;
-  const int KR = p.KR, rot = p.rot;
-  const int TSZ = inv_tile_stride<L>(KR);
-  const int tid = threadIdx.x, nthr = blockDim.x, h = tid & 1;
-  const int P = p.T * p.T, tpc = p.n_img * P;
-  const size_t fstride = size_t(p.n_ch) * tpc;
-  const long ngroups = long(p.n_ch) * p.ngrp;
-  const int npair = (KR + 1) / 2;
-  const float scale = 1.0f / float(L * L);
-  // tasks of passes 1 and 2: h + 2 (q + TQ w), tile q fastest; w is the
-  // column (pass 1) or the row pair (pass 2); threads loop over the tasks
-  float zr[H2], zi[H2];
-
-  // Column w of tile q, rows [h L/2, h L/2 + L/2), summed over the split
-  // partial spectra. Bins are read at a lane offset that steps by one row of
-  // bins per element; the offset is made opaque first, so that the addresses
-  // of all elements are not precomputed and kept across the group loop.
-  using off_t = typename std::conditional<O32, unsigned, size_t>::type;
-  auto at = [&](const float2* base, off_t e) { return O32 ? load_at(base, unsigned(e) * 8u) : base[e]; };
-  auto load = [&](int ch, int t0, int q, int w) {
-    const size_t tb = size_t(ch) * tpc + t0 + q;
-    const off_t row = off_t(size_t(V) * fstride);
-#pragma unroll
-    for (int i = 0; i < H2; ++i) {
-      zr[i] = 0.f;
-      zi[i] = 0.f;
-    }
-    for (int sp = 0; sp < p.nsplit; ++sp) {
-      const float2* base = p.src + size_t(sp) * p.split_stride;
-      if (w > 0) {
-        off_t e = off_t((size_t(h) * H2 * V + w) * fstride + tb);
-        if (O32) asm volatile("" : "+v"(e));
-#pragma unroll
-        for (int i = 0; i < H2; ++i) {
-          const float2 z = at(base, e);
-          e += row;
-          zr[i] += z.x;
-          zi[i] += z.y;
-        }
-      } else {
-        // columns 0 and L/2 together: rows u <= L/2 give b0 + i b1; rows
-        // u > L/2 (lane 1, i > 0) conj b0 + i conj b1 of row L - u. Lane 0
-        // walks rows 0, 1, ..., lane 1 rows L/2, L/2 - 1, ...
-        off_t e = off_t(size_t(h) * H2 * V * fstride + tb);
-        if (O32) asm volatile("" : "+v"(e));
-        const off_t half = off_t(size_t(H2) * fstride);
-#pragma unroll
-        for (int i = 0; i < H2; ++i) {
-          const float2 b0 = at(base, e), b1 = at(base, e + half);
-          if (h) e -= row; else e += row;
-          const bool mirror = h && i > 0;
-          zr[i] += mirror ? b0.x + b1.y : b0.x - b1.y;
-          zi[i] += mirror ? b1.x - b0.y : b0.y + b1.x;
-        }
-      }
-    }
-  };
-  // pass 1 of one task: column inverse; row r becomes kept row (r + rot) mod L
-  auto column = [&](int q, int w) {
-    fft_dif_split<L, +1>(zr, zi, h);  // lane h: row 2m + h at bitrev(m)
-    int qo = q * TSZ + w, ro = h + rot;  // opaque: see load
-    asm volatile("" : "+v"(qo), "+v"(ro));
-    float2* bq = lds + qo;
-#pragma unroll
-    for (int m = 0; m < H2; ++m) {
-      const int rr = (2 * m + ro) & (L - 1);
-      if (rr < KR) bq[rr * RI] = make_float2(zr[bitrev(m, H2)], zi[bitrev(m, H2)]);
-    }
-  };
-  // pass 2 of one task: kept rows 2w, 2w + 1 to real rows, written over their
-  // own storage; column s becomes kept column (s + rot) mod L. Lane 0 takes
-  // bins 0, 1, ..., L/2 - 1 of both rows, lane 1 bins L/2, L/2 - 1, ..., 1
-  // (bins 0 and L/2 being the parts of slot 0); the addresses step by one
-  // slot per element from opaque starting values, and a missing second row
-  // reads the first again and is zeroed, so that neither the compiler's
-  // precomputed addresses nor a branch per element hold registers.
-  auto rows = [&](int q, int w) {
-    const int r0 = 2 * w;
-    const bool has1 = r0 + 1 < KR;
-    int zo = q * TSZ + r0 * RI, co = h + rot, st = h ? -1 : 1, db = has1 ? RI : 0;
-    asm volatile("" : "+v"(zo), "+v"(co), "+v"(st), "+v"(db));
-    const float2* za = lds + zo;
-    const float keep1 = has1 ? 1.f : 0.f, sg = h ? 1.f : -1.f;
-    float xr[H2], xi[H2];
-    {
-      const float2 a0 = za[0], b0 = za[db];
-      xr[0] = h ? a0.y : a0.x;
-      xi[0] = keep1 * (h ? b0.y : b0.x);
-    }
-    int o = h ? H2 - 1 : 1;
-#pragma unroll
-    for (int i = 1; i < H2; ++i) {
-      const float2 a = za[o], bb = za[o + db];
-      o += st;
-      // lane 0: a.x - b.y, a.y + b.x; lane 1: a.x + b.y, b.x - a.y
-      xr[i] = __builtin_fmaf(sg * keep1, bb.y, a.x);
-      xi[i] = __builtin_fmaf(-sg, a.y, keep1 * bb.x);
-      if (i % 8 == 7) asm volatile("" ::: "memory");  // bounds the reads in flight
-    }
-    fft_dif_split<L, +1>(xr, xi, h);  // lane h: L row0[s], L row1[s] at s = 2m + h, position bitrev(m)
-    float* d0 = smem + 2 * zo;
-#pragma unroll
-    for (int m = 0; m < H2; ++m) {
-      const int cc = (2 * m + co) & (L - 1);
-      if (cc < KR) {
-        d0[cc] = xr[bitrev(m, H2)] * scale;
-        if (has1) d0[2 * RI + cc] = xi[bitrev(m, H2)] * scale;
-      }
-    }
-  };
-
-  const GroupWalk wk = group_walk(ngroups, true);
-  for (long g = wk.g; g < wk.end; g += wk.step) {
-    const int ch = int(g / p.ngrp), t0 = int(g % p.ngrp) * p.TQ;
-    const int nq = min(p.TQ, tpc - t0);
-    for (int task = tid; task < L * p.TQ; task += nthr) {
-      const int q = (task >> 1) % p.TQ, w = (task >> 1) / p.TQ;
-      if (q >= nq) continue;
-      load(ch, t0, q, w);
-      column(q, w);
-    }
-    __syncthreads();
-    for (int task = tid; task < 2 * npair * p.TQ; task += nthr) {
-      const int q = (task >> 1) % p.TQ, w = (task >> 1) / p.TQ;
-      if (q < nq) rows(q, w);
-    }
-    __syncthreads();
-    const int H = p.H;
-    const int wave = tid >> 6, lane = tid & 63, nwave = nthr >> 6;
-    if (MODE == 2) {
-      // kept KR x KR of every tile to the scratch, tile after tile
-      float* ob = p.tiles + (size_t(ch) * tpc + t0) * KR * KR;
-      const SmallDiv div_k(KR);
-      for (int qq = wave; qq < nq; qq += nwave) {
-        const float* lt = ldf + 2 * qq * TSZ;
-        float* ot = ob + size_t(qq) * KR * KR;
-        for (int e = lane; e < KR * KR; e += 64) {
-          const int rr = div_k(e), cc = e - rr * KR;
-          ot[e] = lt[2 * rr * RI + cc];
-        }
-      }
-    } else if (MODE == 0) {
-      // kept KR x KR of every tile to its block: a wave per tile (decoded
-      // once, wave-uniform), lanes over the block in row order
-      const SmallDiv div_k(KR);
-      for (int qq = wave; qq < nq; qq += nwave) {
-        const int t = t0 + qq, img = t / P, pp = t - img * P;
-        const int pr = pp / p.T, qc = pp - pr * p.T;
-        const int nrow = min(KR, H - pr * p.pitch), ncol = min(KR, H - qc * p.pitch);
-        float* oblk = p.dst + ((size_t(img) * p.n_ch + ch) * H + pr * p.pitch) * H + qc * p.pitch;
-        const float* lt = ldf + 2 * qq * TSZ;
-        for (int e = lane; e < KR * nrow; e += 64) {
-          const int rr = div_k(e), cc = e - rr * KR;
-          if (cc < ncol) oblk[rr * H + cc] = lt[2 * rr * RI + cc];
-        }
-      }
-    } else {
-      overlap_plane_out<L, false>(p, ldf, TSZ, ch, t0, wave, lane, nwave);
-    }
-    __syncthreads();
-  }
-}
-
-// ---------------------------------------------------------------------------
-// inverse at L = 64 with a whole 64-point sequence per lane: a lane inverts
-// one column of a tile (pass 1), then one pair of rows (pass 2), in 128
-// registers, where the kernel above splits each sequence over a lane pair.
-// No first stage runs across a pair (about 0.7 of the vector instructions
-// per transform). The 32 tasks per tile and pass of a group of eight tiles
+// real columns. Pass 2 inverts pairs of rows to real rows, written over their
+// own storage. The 32 tasks per tile and pass of a group of eight tiles
 // fill four waves, half the workgroup, and the halves alternate: while one
 // transforms group i, the other loads the columns of group i + 1 into its
 // registers, which then have passes 2 and 3 of group i to arrive. A nine-tile
@@ -688,13 +337,15 @@ __global__ void __launch_bounds__(kBigInvThreads) big_irfft2_kernel(BigInvParams
 // conditions that are uniform, makes the compiler keep more of the
 // transform's values live across the stores, and spill), pass 2 runs on the
 // row pairs that hold kept rows only, and the output pass applies the
-// rotation and the 1/L^2 scale. MODE as for the kernel above; SPLIT: more
+// rotation and the 1/L^2 scale. MODE: the kernel's pass 3 (0 crop, 1
+// overlap-add of one-group planes, 2 tiles to the scratch), fixed per instance
+// so that each carries only the registers of its own output code; SPLIT: more
 // than one partial spectrum to sum (the weight gradient's split), loaded in
 // batches of 16 rows so that the partial sums and the loads in flight fit
 // the registers.
 template <bool O32, int MODE, bool SPLIT>
 __global__ void __launch_bounds__(512) big_irfft2_lane_kernel(BigInvParams p) {
-  constexpr int L = 64, H2 = L / 2, V = L / 2 + 1, RI = Big<L>::RI, HALF = 256;
+  constexpr int L = 64, H2 = L / 2, V = L / 2 + 1, RI = Big::RI, HALF = 256;
   extern __shared__ float smem[];
   float2* lds = reinterpret_cast<float2*>(smem);
   const float* ldf = smem;
@@ -865,7 +516,7 @@ __global__ void __launch_bounds__(512) big_irfft2_lane_kernel(BigInvParams p) {
     }
     __syncthreads();
     if (MODE == 1) {
-      overlap_plane_out<L, true>(p, ldf, TSZ, ch, t0, wave, lane, nwave);
+      overlap_plane_out(p, ldf, TSZ, ch, t0, wave, lane, nwave);
     } else if (rot == 0) {
       crop(ch, t0, nq, wave, lane, nwave, std::false_type{});
     } else {
@@ -912,18 +563,6 @@ __global__ void __launch_bounds__(256) overlap_gather_kernel(BigInvParams p, int
 // ---------------------------------------------------------------------------
 // launchers
 
-int cu_count() {
-  static int cached[64] = {0};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-  if (!cached[dev]) {
-    int cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
-    cached[dev] = cus;
-  }
-  return cached[dev];
-}
-
 // Waves of these kernels resident on a CU: every instance takes more than 128
 // registers per lane, which leaves two waves on each of the four SIMDs.
 constexpr int kBigWavesPerCu = 8;
@@ -934,37 +573,32 @@ unsigned persistent_grid(long ngroups, size_t lds, int nthr) {
   const long by_lds = long(kBigLds / std::max<size_t>(lds, 1));
   const long by_waves = kBigWavesPerCu / std::max(1, (nthr + 63) / 64);
   const long per_cu = std::max<long>(1, std::min(by_lds, by_waves));
-  long nwg = std::min<long>(per_cu * cu_count(), (ngroups + 7) / 8 * 8);
+  long nwg = std::min<long>(per_cu * device_cus(), (ngroups + 7) / 8 * 8);
   nwg = std::max<long>(8, nwg / 8 * 8);
   return unsigned(nwg);
 }
 
-// tiles per group: runs of eight (64-byte segments of a bin) at L = 64, or
-// whole planes where fewer fit; two at L = 128
-template <int L>
+// tiles per group: runs of eight (64-byte segments of a bin), or whole planes
+// where fewer fit
 int group_tiles(int P, long tpc) {
-  int tq = L == 64 ? OAA_BIG_TQ : 2;
+  int tq = OAA_BIG_TQ;
   if (P > 1 && P < tq) tq = P * (tq / P);
   return int(std::max<long>(1, std::min<long>(tq, tpc)));
 }
 
-template <int L, bool PF>
-hipError_t launch_big_fwd_LP(const BigFwdParams& p, size_t lds, long ngroups, hipStream_t s) {
-  constexpr int V = Big<L>::V;
-  // one past the largest element the layout addresses
-  const long tpc = long(p.n_img) * p.T * p.T;
-  const size_t end = size_t(L * V - 1) * p.bs + size_t(p.n_ch - 1) * p.cs + size_t((tpc - 1) / p.run) * p.rs +
-                     size_t(std::min<long>(p.run, tpc));
-  const bool o32 = end * 8 < (size_t(1) << 32);
-  auto kern = o32 ? big_rfft2_kernel<L, true, PF> : big_rfft2_kernel<L, false, PF>;
-  const hipError_t e = allow_lds(kern, kBigLds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(persistent_grid(ngroups, lds, L * p.TQ)), dim3(L * p.TQ), lds, s, p);
-  return hipGetLastError();
-}
+// Forward tiles up to which L = 64 takes the kernels that spread a transform
+// over lanes: one lane per transform needs about four groups of eight tiles
+// per two CUs to overlap its halves. Measured: 100 tiles 6.4 against 13.7 us,
+// 400 tiles 8.1 against 14.2, 2304 tiles 25.1 against 25.2, 27648 tiles 225
+// against 208.
+constexpr long kWideFwdTiles = 1536;
+// The same for the inverse. Measured: crops of 100 tiles 7.9 against 11.1 us,
+// 192 tiles of eight partial sums 28 against 43, 400 tiles 9.5 against 11.3,
+// 1000 tiles 14.7 against 11.9; planes of one tile as the crops, planes of
+// nine 23 against 17.
+constexpr long kWideInvTiles = 512;
 
-template <int L>
-hipError_t launch_big_fwd_L(BigFwdParams p, hipStream_t s) {
+hipError_t launch_big_fwd(int L, BigFwdParams p, hipStream_t s) {
   if (p.S < 1 || p.S > L || p.T < 1 || p.H < 1 || size_t(p.H) * p.H * 4 >= (size_t(1) << 31))
     return hipErrorInvalidValue;
   const int P = p.T * p.T;
@@ -977,62 +611,26 @@ hipError_t launch_big_fwd_L(BigFwdParams p, hipStream_t s) {
     p.cs = size_t(tpc);
   }
   if (p.run < 1) return hipErrorInvalidValue;
-  p.TQ = group_tiles<L>(P, tpc);
+  if (L != Big::L || tpc * p.n_ch <= kWideFwdTiles) return launch_wide_rfft2(L, p, s);
+  p.TQ = group_tiles(P, tpc);
   p.ngrp = int((tpc + p.TQ - 1) / p.TQ);
-  const size_t lds = size_t(fwd_tile_stride<L>()) * p.TQ * 8;
-  // one task per thread (group_tiles keeps L TQ within a workgroup)
-  if (lds > kBigLds || L * p.TQ > big_threads<L, true>()) return hipErrorInvalidConfiguration;
-  const long ngroups = long(p.n_ch) * p.ngrp;
-  // at L = 64 the alternating halves need two groups or more per workgroup
-  // (one per CU) to overlap anything; smaller launches take the lane pairs
-  // (measured at the 224 x 224 RGB layer: kernel spectra, 24 groups, 0.017
-  // against 0.025 ms)
-  if constexpr (L == 64) {
-    if (ngroups < 2L * cu_count()) return launch_big_fwd_LP<L, true>(p, lds, ngroups, s);
-    constexpr int V = Big<L>::V;
-    const size_t end = size_t(L * V - 1) * p.bs + size_t(p.n_ch - 1) * p.cs + size_t((tpc - 1) / p.run) * p.rs +
-                       size_t(std::min<long>(p.run, tpc));
-    // the planes one group's windows read: tiles of at most TQ images
-    const size_t span = (size_t(p.TQ - 1) * p.n_ch + 1) * size_t(p.H) * p.H * 4;
-    const bool narrow = end * 8 < (size_t(1) << 32) && span < size_t(kOutOfRange);
-    auto kern = narrow ? big_rfft2_lane_kernel<false> : big_rfft2_lane_kernel<true>;
-    const hipError_t e = allow_lds(kern, kBigLds);
-    if (e != hipSuccess) return e;
-    const size_t lane_lds = size_t(lane_tile_stride()) * p.TQ * 8;
-    if (lane_lds > kBigLds) return hipErrorInvalidConfiguration;
-    constexpr int nthr = 512;  // two halves of four waves: 32 TQ <= 256 tasks per pass
-    hipLaunchKernelGGL(kern, dim3(persistent_grid(ngroups, lane_lds, nthr)), dim3(nthr), lane_lds, s, p);
-    return hipGetLastError();
-  } else {
-    return launch_big_fwd_LP<L, false>(p, lds, ngroups, s);
-  }
-}
-
-template <int L, int MODE>
-hipError_t launch_big_inv_LM(const BigInvParams& p, size_t lds, long ngroups, hipStream_t s) {
-  constexpr int V = Big<L>::V;
-  const bool o32 =
-      (size_t(L) * V * size_t(p.n_ch) * size_t(p.n_img) * p.T * p.T + size_t(p.nsplit - 1) * p.split_stride) * 8 <
-      (size_t(1) << 32);
-  auto kern = o32 ? big_irfft2_kernel<L, true, MODE> : big_irfft2_kernel<L, false, MODE>;
+  // one past the largest element the layout addresses
+  const size_t end = size_t(Big::L * Big::V - 1) * p.bs + size_t(p.n_ch - 1) * p.cs +
+                     size_t((tpc - 1) / p.run) * p.rs + size_t(std::min<long>(p.run, tpc));
+  // the planes one group's windows read: tiles of at most TQ images
+  const size_t span = (size_t(p.TQ - 1) * p.n_ch + 1) * size_t(p.H) * p.H * 4;
+  const bool narrow = end * 8 < (size_t(1) << 32) && span < size_t(kOutOfRange);
+  auto kern = narrow ? big_rfft2_lane_kernel<false> : big_rfft2_lane_kernel<true>;
   const hipError_t e = allow_lds(kern, kBigLds);
   if (e != hipSuccess) return e;
-  const int nthr = std::min(L * p.TQ, kBigInvThreads);
-  hipLaunchKernelGGL(kern, dim3(persistent_grid(ngroups, lds, nthr)), dim3(nthr), lds, s, p);
+  const size_t lds = size_t(lane_tile_stride()) * p.TQ * 8;
+  if (lds > kBigLds) return hipErrorInvalidConfiguration;
+  constexpr int nthr = 512;  // two halves of four waves: 32 TQ <= 256 tasks per pass
+  hipLaunchKernelGGL(kern, dim3(persistent_grid(long(p.n_ch) * p.ngrp, lds, nthr)), dim3(nthr), lds, s, p);
   return hipGetLastError();
 }
 
-template <int L>
-hipError_t launch_big_inv_LS(const BigInvParams& p, size_t lds, long ngroups, hipStream_t s) {
-  switch (p.overlap) {
-    case 0: return launch_big_inv_LM<L, 0>(p, lds, ngroups, s);
-    case 1: return launch_big_inv_LM<L, 1>(p, lds, ngroups, s);
-    case 2: return launch_big_inv_LM<L, 2>(p, lds, ngroups, s);
-    default: return hipErrorInvalidValue;
-  }
-}
-
-// L = 64: one sequence per lane, tiles of whole L x (L/2 + 1) slots
+// One sequence per lane, tiles of whole L x (L/2 + 1) slots
 template <bool O32>
 hipError_t launch_big_inv_lane_O(const BigInvParams& p, size_t lds, long ngroups, hipStream_t s) {
   void (*kern)(BigInvParams) = nullptr;
@@ -1049,17 +647,15 @@ hipError_t launch_big_inv_lane_O(const BigInvParams& p, size_t lds, long ngroups
 }
 
 hipError_t launch_big_inv_lane(const BigInvParams& p, long ngroups, hipStream_t s) {
-  constexpr int L = 64;
   const size_t lds = size_t(lane_tile_stride()) * p.TQ * 8;
-  if (lds > kBigLds || p.TQ > Big<L>::TQ_MAX) return hipErrorInvalidConfiguration;
+  if (lds > kBigLds || p.TQ > Big::TQ_MAX) return hipErrorInvalidConfiguration;
   const size_t tpc = size_t(p.n_img) * p.T * p.T;
-  const bool o32 = (size_t(L) * Big<L>::V * size_t(p.n_ch) * tpc + size_t(p.nsplit - 1) * p.split_stride) * 8 <
+  const bool o32 = (size_t(Big::L) * Big::V * size_t(p.n_ch) * tpc + size_t(p.nsplit - 1) * p.split_stride) * 8 <
                    (size_t(1) << 32);
   return o32 ? launch_big_inv_lane_O<true>(p, lds, ngroups, s) : launch_big_inv_lane_O<false>(p, lds, ngroups, s);
 }
 
-template <int L>
-hipError_t launch_big_inv_L(BigInvParams p, hipStream_t s) {
+hipError_t launch_big_inv(int L, BigInvParams p, hipStream_t s) {
   if (p.KR < 1 || p.KR > L || p.rot < 0 || p.rot >= L || p.T < 1 || p.H < 1 || p.nsplit < 1 ||
       p.H >= 65536 || size_t(p.H) * p.H >= (size_t(1) << 31))
     return hipErrorInvalidValue;
@@ -1068,30 +664,28 @@ hipError_t launch_big_inv_L(BigInvParams p, hipStream_t s) {
   if (tpc < 1 || tpc > 0x7fffffffL) return hipErrorInvalidValue;
   bool two_step = false;
   if (p.overlap) {
-    if (p.pitch < 1 || p.off < 0 || p.H + p.off >= 65536) return hipErrorInvalidValue;
-    if (P <= Big<L>::TQ_MAX) {
-      p.TQ = P;  // one plane per group
-    } else {
+    if (p.pitch < 1 || p.off < 0 || p.H + p.off >= 65536 || p.nsplit != 1) return hipErrorInvalidValue;
+    if (!p.tiles && big_overlap_few(L, long(p.n_img) * p.n_ch, p.T)) {
+      p.overlap = 3;
+      return launch_wide_irfft2(L, p, s);
+    }
+    if (!big_overlap_supported(L, p.T)) {
       // keep every tile's KR x KR in the scratch, then add in a second kernel
       if (!p.tiles || long(p.KR) * p.KR >= 65536) return hipErrorInvalidValue;
       two_step = true;
       p.overlap = 2;
-      p.TQ = group_tiles<L>(P, tpc);
     }
-  } else {
-    if (p.pitch != p.KR) return hipErrorInvalidValue;
-    p.TQ = group_tiles<L>(P, tpc);
-    if (long(p.KR) * p.KR * p.TQ >= 65536) return hipErrorInvalidValue;
+  } else if (p.pitch != p.KR) {
+    return hipErrorInvalidValue;
   }
-  p.ngrp = int((tpc + p.TQ - 1) / p.TQ);
-  const size_t lds = size_t(inv_tile_stride<L>(p.KR)) * p.TQ * 8;
-  if (lds > kBigLds) return hipErrorInvalidConfiguration;
-  const long ngroups = long(p.n_ch) * p.ngrp;
   hipError_t e = hipSuccess;
-  if constexpr (L == 64) {
-    e = launch_big_inv_lane(p, ngroups, s);
+  if (L != Big::L || (tpc * p.n_ch <= kWideInvTiles && (p.overlap != 1 || P == 1))) {
+    e = launch_wide_irfft2(L, p, s);
   } else {
-    e = launch_big_inv_LS<L>(p, lds, ngroups, s);
+    p.TQ = p.overlap == 1 ? P : group_tiles(P, tpc);  // overlap-add in a group: one plane
+    if (!p.overlap && long(p.KR) * p.KR * p.TQ >= 65536) return hipErrorInvalidValue;
+    p.ngrp = int((tpc + p.TQ - 1) / p.TQ);
+    e = launch_big_inv_lane(p, long(p.n_ch) * p.ngrp, s);
   }
   if (e != hipSuccess || !two_step) return e;
   // second step: about 8 rows per workgroup
@@ -1104,26 +698,38 @@ hipError_t launch_big_inv_L(BigInvParams p, hipStream_t s) {
 
 }  // namespace
 
-hipError_t launch_big_rfft2(int L, const BigFwdParams& p, hipStream_t s) {
-  switch (L) {
-    case 64: return launch_big_fwd_L<64>(p, s);
-    case 128: return launch_big_fwd_L<128>(p, s);
-    default: return hipErrorInvalidValue;
+int device_cus() {
+  static int cached[64] = {0};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+  if (!cached[dev]) {
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
+    cached[dev] = cus;
   }
+  return cached[dev];
+}
+
+hipError_t launch_big_rfft2(int L, const BigFwdParams& p, hipStream_t s) {
+  return L == 64 || L == 128 ? launch_big_fwd(L, p, s) : hipErrorInvalidValue;
 }
 
 hipError_t launch_big_irfft2(int L, const BigInvParams& p, hipStream_t s) {
-  switch (L) {
-    case 64: return launch_big_inv_L<64>(p, s);
-    case 128: return launch_big_inv_L<128>(p, s);
-    default: return hipErrorInvalidValue;
-  }
+  return L == 64 || L == 128 ? launch_big_inv(L, p, s) : hipErrorInvalidValue;
+}
+
+// The block-by-block kernel inverts each tile four times, the one with a
+// workgroup per block row about three: it pays while its blocks are at most
+// one per CU. Measured, with the stage's events: one 224 x 224 plane of 16
+// tiles 15 against 25 us, 256 tiles 17 against 26, 512 tiles 28 against 26,
+// 1024 tiles 51 against 32.
+bool big_overlap_few(int L, long n_planes, int T) {
+  return L == 64 && !big_overlap_supported(L, T) && n_planes * T * T <= 256;
 }
 
 bool big_overlap_supported(int L, int T) {
-  if (L == 64) return T * T <= Big<64>::TQ_MAX;
-  if (L == 128) return T * T <= Big<128>::TQ_MAX;
-  return false;
+  // whole tiles in LDS: nine of side 64, one of side 128
+  return L == 64 ? T <= Big::SIDE_MAX : L == 128 && T == 1;
 }
 
 }  // namespace oaa

@@ -1,0 +1,496 @@
+// Transforms of side L = 128, and of side 64 in launches of few tiles
+// (arXiv:1601.06815, Section 2: block division, zero padding, the per-block
+// transforms and the overlap-add; Section 3.3 for the transform sides of large
+// kernels), with each L-point transform spread over lanes.
+//
+// L = N1 x 8. With n = 8 n1 + n2 and k = k1 + N1 k2,
+//   X[k1 + N1 k2] = sum_n2 w8^(n2 k2) ( wL^(n2 k1) sum_n1 wN1^(n1 k1) x[8 n1 + n2] ),
+// so a transform takes two passes over LDS: N1-point transforms over the
+// elements of one n2 with a twiddle, then 8-point transforms over n2. Both
+// passes read and write the same slots of a sequence, and coefficient k ends
+// at position 8 (k mod N1) + k / N1 (`place`). A tile's 2-D transform is four
+// such passes, on 8 L/2 tasks of N1 points and N1 L/2 tasks of 8 points: one
+// tile keeps 8 (L = 128) waves busy in about 60 registers, and the chain that
+// a lane runs is short. What bounds a launch of few tiles is that chain.
+// Transforms held by lane pairs (64 points per lane and pass, 256 registers
+// with 600 bytes of them spilled at L = 128, two waves per tile) took 62 us for
+// the forward inverse of 100 tiles of 128 x 128 and 45 us for the one tile of
+// the error propagation, now 23 and 16; and 3.8 ms for 16384 tiles, now 1.5.
+#include <algorithm>
+
+#include "fft_core.hpp"
+#include "oaa_internal.hpp"
+#include "tile_common.hpp"
+
+namespace oaa {
+
+namespace {
+
+using namespace tile;
+
+constexpr size_t kWideLds = 160 * 1024;  // LDS of one CU
+constexpr int kWideMaxThreads = 1024;
+
+template <int L>
+struct Wide {
+  static constexpr int N1 = L / 8, H2 = L / 2, V = L / 2 + 1;
+  static constexpr int RS = H2 + 1;          // LDS row stride (complex)
+  static constexpr int TS = L * RS | 1;      // LDS per tile (complex, odd)
+  static constexpr int TASKS = 8 * H2;       // N1-point tasks of a pass
+  static constexpr int TASKS8 = N1 * H2;     // 8-point tasks of a pass
+  __device__ static constexpr int place(int k) { return 8 * (k % N1) + k / N1; }
+};
+
+// (re + i im) w_L^(SIGN n2 k1), w_L from the table of cosines and sines in LDS
+template <int L, int SIGN>
+__device__ __forceinline__ float2 turned(const float2* tw, int n2, int k1, float re, float im) {
+  if (k1 == 0) return make_float2(re, im);
+  const float2 w = tw[n2 * k1];
+  const float s = SIGN > 0 ? w.y : -w.y;
+  return make_float2(__builtin_fmaf(re, w.x, -im * s), __builtin_fmaf(re, s, im * w.x));
+}
+
+// cos and sin of 2 pi k / L, k < L, into LDS
+template <int L>
+__device__ __forceinline__ void load_twiddles(float2* tw) {
+  for (int k = threadIdx.x; k < L; k += blockDim.x) tw[k] = make_float2(tw::kTable<L>.c[k], tw::kTable<L>.s[k]);
+}
+
+// 8-point pass over n2 of the sequence element (k1, n2) at z[(8 k1 + n2) stride]
+template <int SIGN>
+__device__ __forceinline__ void pass8(float2* z, int stride) {
+  float re[8], im[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const float2 v = z[i * stride];
+    re[i] = v.x;
+    im[i] = v.y;
+  }
+  fft_dif<8, SIGN, false>(re, im);
+#pragma unroll
+  for (int k = 0; k < 8; ++k) z[k * stride] = make_float2(re[bitrev(k, 8)], im[bitrev(k, 8)]);
+}
+
+// ---------------------------------------------------------------------------
+// forward: windows of planes -> half spectra
+//
+// Columns: z = x[., j] + i x[., j + L/2] along the rows; the real columns'
+// spectra are C_j[u] = (Z[u] + conj Z[-u]) / 2 and C_{j+L/2}[u] =
+// (Z[u] - conj Z[-u]) / (2i), taken as the row pass reads them. Rows: row u in
+// [1, L/2) along the columns gives bins (u, v), v <= L/2, and (L - u, v) =
+// conj X[u][L - v], 0 < v < L/2 (the other bins of rows past L/2 are
+// conjugates that nothing reads); it uses the storage of LDS rows u and L - u.
+// Rows 0 and L/2 are real and go through one transform as row 0.
+template <int L>
+__global__ void __launch_bounds__(kWideMaxThreads) wide_rfft2_kernel(BigFwdParams p) {
+  using W = Wide<L>;
+  constexpr int N1 = W::N1, H2 = W::H2, V = W::V, RS = W::RS;
+  extern __shared__ float smem[];
+  float2* tw = reinterpret_cast<float2*>(smem);
+  float2* lds = tw + L;
+  const int tid = threadIdx.x, nthr = blockDim.x, TQ = p.TQ;
+  const int P = p.T * p.T, tpc = p.n_img * P;
+  const size_t bs = p.bs;
+  const long ngroups = long(p.n_ch) * p.ngrp;
+  load_twiddles<L>(tw);
+  __syncthreads();
+  for (long g = long(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8; g < ngroups; g += gridDim.x) {
+    const int ch = int(g / p.ngrp), t0 = int(g % p.ngrp) * TQ;
+    const int nq = min(TQ, tpc - t0);
+    // columns, N1 points: lanes over the columns (a wave holds one tile)
+    for (int task = tid; task < nq * W::TASKS; task += nthr) {
+      const int j = task % H2, n2 = (task / H2) % 8, q = task / W::TASKS;
+      const int t = t0 + q, img = t / P, pp = t - img * P;
+      const int pr = pp / p.T, qc = pp - pr * p.T;
+      const float* plane = p.src + (size_t(img) * p.n_ch + ch) * size_t(p.H) * size_t(p.H);
+      const __amdgpu_buffer_rsrc_t rs = buffer_resource(plane, unsigned(p.H) * unsigned(p.H) * 4u);
+      const int ca = qc * p.pitch - p.off + j, cb = ca + H2, gr0 = pr * p.pitch - p.off + n2;
+      const bool oka = j < p.S && unsigned(ca) < unsigned(p.H);
+      const bool okb = j + H2 < p.S && unsigned(cb) < unsigned(p.H);
+      float re[N1], im[N1];
+#pragma unroll
+      for (int i = 0; i < N1; ++i) {
+        const int gr = gr0 + 8 * i;
+        const bool okr = 8 * i + n2 < p.S && unsigned(gr) < unsigned(p.H);
+        re[i] = buffer_load_f1(rs, okr && oka ? unsigned(gr * p.H + ca) * 4u : kOutOfRange);
+        im[i] = buffer_load_f1(rs, okr && okb ? unsigned(gr * p.H + cb) * 4u : kOutOfRange);
+      }
+      fft_dif<N1, -1, false>(re, im);
+      float2* z = lds + q * W::TS + n2 * RS + j;
+#pragma unroll
+      for (int k = 0; k < N1; ++k)
+        z[8 * k * RS] = turned<L, -1>(tw, n2, k, re[bitrev(k, N1)], im[bitrev(k, N1)]);
+    }
+    __syncthreads();
+    // columns, 8 points
+    for (int task = tid; task < nq * W::TASKS8; task += nthr) {
+      const int j = task % H2, k1 = (task / H2) % N1, q = task / W::TASKS8;
+      pass8<-1>(lds + q * W::TS + 8 * k1 * RS + j, RS);
+    }
+    __syncthreads();
+    // rows, N1 points: lanes over n2, then the rows
+    for (int task = tid; task < nq * W::TASKS; task += nthr) {
+      const int n2 = task % 8, u = (task / 8) % H2, q = task / W::TASKS;
+      float2* za = lds + q * W::TS + W::place(u) * RS + n2;
+      float2* zb = lds + q * W::TS + W::place(u ? L - u : H2) * RS + n2;
+      float re[N1], im[N1];
+#pragma unroll
+      for (int i = 0; i < N1 / 2; ++i) {
+        const float2 a = za[8 * i], c = zb[8 * i];
+        re[i] = u ? 0.5f * (a.x + c.x) : a.x;
+        im[i] = u ? 0.5f * (a.y - c.y) : c.x;
+        re[N1 / 2 + i] = u ? 0.5f * (a.y + c.y) : a.y;
+        im[N1 / 2 + i] = u ? 0.5f * (c.x - a.x) : c.y;
+      }
+      fft_dif<N1, -1, false>(re, im);
+#pragma unroll
+      for (int k = 0; k < N1 / 2; ++k) {
+        za[8 * k] = turned<L, -1>(tw, n2, k, re[bitrev(k, N1)], im[bitrev(k, N1)]);
+        zb[8 * k] = turned<L, -1>(tw, n2, k + N1 / 2, re[bitrev(k + N1 / 2, N1)], im[bitrev(k + N1 / 2, N1)]);
+      }
+    }
+    __syncthreads();
+    // rows, 8 points, and the bins: lanes over the group's tiles, then the rows
+    for (int task = tid; task < TQ * W::TASKS8; task += nthr) {
+      const int q = task % TQ, u = (task / TQ) % H2, k1 = task / (TQ * H2);
+      if (q >= nq) continue;
+      float2* z = lds + q * W::TS + W::place(k1 < N1 / 2 ? u : u ? L - u : H2) * RS + 8 * (k1 % (N1 / 2));
+      if (u == 0) {  // the packed row stays in LDS
+        pass8<-1>(z, 1);
+        continue;
+      }
+      float re[8], im[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        re[i] = z[i].x;
+        im[i] = z[i].y;
+      }
+      fft_dif<8, -1, false>(re, im);
+      const int t = t0 + q;
+      float2* out = p.dst + size_t(ch) * p.cs + size_t(t / p.run) * p.rs + size_t(t % p.run);
+      float2* o1 = out + (size_t(u) * V + k1) * bs;            // (u, k1 + N1 k2)
+      float2* o2 = out + (size_t(L - u) * V + L - k1) * bs;    // (L - u, L - k1 - N1 k2)
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const float r = re[bitrev(k, 8)], i = im[bitrev(k, 8)];
+        if (k < 4 || (k == 4 && k1 == 0))
+          o1[size_t(k * N1) * bs] = make_float2(r, i);
+        else
+          *(o2 - size_t(k * N1) * bs) = make_float2(r, -i);
+      }
+    }
+    __syncthreads();
+    // the packed row gives rows 0 and L/2
+    for (int task = tid; task < TQ * V; task += nthr) {
+      const int q = task % TQ, v = task / TQ;
+      if (q >= nq) continue;
+      const float2* z0 = lds + q * W::TS + W::place(0) * RS;
+      const float2* z1 = lds + q * W::TS + W::place(H2) * RS;
+      auto at = [&](int k) {
+        const int pos = W::place(k);
+        return pos < H2 ? z0[pos] : z1[pos - H2];
+      };
+      const float2 a = at(v), c = at((L - v) % L);
+      const int t = t0 + q;
+      float2* out = p.dst + size_t(ch) * p.cs + size_t(t / p.run) * p.rs + size_t(t % p.run);
+      out[size_t(v) * bs] = make_float2(0.5f * (a.x + c.x), 0.5f * (a.y - c.y));
+      out[(size_t(H2) * V + v) * bs] = make_float2(0.5f * (a.y + c.y), 0.5f * (c.x - a.x));
+    }
+    __syncthreads();
+  }
+}
+
+// ---------------------------------------------------------------------------
+// inverse: half spectra -> kept part of every tile (crop), or the plane the
+// tiles overlap-add to
+//
+// Columns w < L/2 along u; column 0 carries the real columns 0 and L/2
+// together as h0[u] + i h1[u] (rows past L/2 rebuilt as the conjugates of rows
+// L - u, which are not stored). Then pairs of kept rows as one complex
+// sequence, in the storage of the pair's two LDS rows. Rows and columns stay at
+// their inverse index, kept index (r + rot) mod L; the output pass scales.
+// MODE: 0 crop, 1 overlap-add of planes whose tiles fit the group, 2 tiles to
+// the scratch, 3 overlap-add by output block: a group is block (P, Q) of a
+// plane, To x To blocks per plane, and its tiles the four that reach the block,
+// (P - 1 + q / 2, Q - 1 + q % 2), each block's tiles inverted anew. Every sum
+// is taken in a fixed order.
+template <int L, int MODE>
+__global__ void __launch_bounds__(kWideMaxThreads) wide_irfft2_kernel(BigInvParams p) {
+  using W = Wide<L>;
+  constexpr int N1 = W::N1, H2 = W::H2, V = W::V, RS = W::RS;
+  extern __shared__ float smem[];
+  float2* tw = reinterpret_cast<float2*>(smem);
+  float2* lds = tw + L;
+  const float* ldf = reinterpret_cast<const float*>(lds);
+  const int tid = threadIdx.x, nthr = blockDim.x, TQ = p.TQ;
+  const int KR = p.KR, rot = p.rot, npair = (KR + 1) / 2;
+  const int P = p.T * p.T, tpc = p.n_img * P;
+  const size_t fstride = size_t(p.n_ch) * tpc;
+  const long ngroups = long(p.n_ch) * p.ngrp;
+  const float scale = 1.0f / float(L * L);
+  // inverse index of kept index k
+  auto inverse = [&](int k) { return (k - rot) & (L - 1); };
+  load_twiddles<L>(tw);
+  __syncthreads();
+  for (long g = long(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8; g < ngroups; g += gridDim.x) {
+    const int ch = int(g / p.ngrp);
+    // MODE 3: output block (Pb, Qb) of image t0 / P
+    const int blk = int(g % p.ngrp), To = p.To, Pb = MODE == 3 ? blk / To % To : 0, Qb = MODE == 3 ? blk % To : 0;
+    const int t0 = MODE == 3 ? blk / (To * To) * P : blk * TQ;
+    const int nq = MODE == 3 ? 4 : min(TQ, tpc - t0);
+    // tile q of the group, and whether there is one
+    auto tile_at = [&](int q) {
+      return MODE == 3 ? t0 + (Pb - 1 + q / 2) * p.T + Qb - 1 + q % 2 : t0 + q;
+    };
+    auto has = [&](int q) {
+      return MODE == 3 ? unsigned(Pb - 1 + q / 2) < unsigned(p.T) && unsigned(Qb - 1 + q % 2) < unsigned(p.T) : q < nq;
+    };
+    // columns, N1 points: lanes over the group's tiles, then the columns;
+    // column 0 last, so that its other arithmetic meets one wave only
+    for (int task = tid; task < TQ * W::TASKS; task += nthr) {
+      const int q = task % TQ, rest = task / TQ;
+      if (!has(q)) continue;
+      const bool edge = rest >= 8 * (H2 - 1);
+      const int w = edge ? 0 : 1 + rest % (H2 - 1), n2 = edge ? rest - 8 * (H2 - 1) : rest / (H2 - 1);
+      const float2* src = p.src + size_t(ch) * tpc + tile_at(q);
+      float re[N1], im[N1];
+#pragma unroll
+      for (int i = 0; i < N1; ++i) re[i] = im[i] = 0.f;
+      // addresses step from an opaque pointer, so that those of all elements
+      // are not held at once
+      const size_t step = size_t(8 * V) * fstride;
+      for (int sp = 0; sp < p.nsplit; ++sp) {
+        const float2* b = src + size_t(sp) * p.split_stride + (size_t(n2) * V + w) * fstride;
+        asm volatile("" : "+v"(b));
+        if (!edge) {
+#pragma unroll
+          for (int i = 0; i < N1; ++i, b += step) {
+            const float2 z = *b;
+            re[i] += z.x;
+            im[i] += z.y;
+          }
+        } else {
+#pragma unroll
+          for (int i = 0; i < N1; ++i) {
+            // rows up to L/2, then L - u for the rows u = 8 i + n2 past it
+            if (i == N1 / 2 && n2 != 0) b -= size_t(2 * n2) * V * fstride;
+            const bool mirror = i > N1 / 2 || (i == N1 / 2 && n2 != 0);
+            const float2 b0 = b[0], b1 = b[size_t(H2) * fstride];
+            re[i] += mirror ? b0.x + b1.y : b0.x - b1.y;
+            im[i] += mirror ? b1.x - b0.y : b0.y + b1.x;
+            if (i < N1 / 2) b += step; else b -= step;
+          }
+        }
+      }
+      fft_dif<N1, +1, false>(re, im);
+      float2* z = lds + q * W::TS + n2 * RS + w;
+#pragma unroll
+      for (int k = 0; k < N1; ++k)
+        z[8 * k * RS] = turned<L, +1>(tw, n2, k, re[bitrev(k, N1)], im[bitrev(k, N1)]);
+    }
+    __syncthreads();
+    // columns, 8 points
+    for (int task = tid; task < nq * W::TASKS8; task += nthr) {
+      const int w = task % H2, k1 = (task / H2) % N1, q = task / W::TASKS8;
+      pass8<+1>(lds + q * W::TS + 8 * k1 * RS + w, RS);
+    }
+    __syncthreads();
+    // row pairs, N1 points: lanes over n2, then the pairs. A task reads the
+    // slots of n2 and of 8 - n2, which another lane of the same eight writes:
+    // all read before any writes.
+    const int ntask = nq * npair * 8;
+    for (int base = 0; base < ntask; base += nthr) {
+      const int task = base + tid;
+      const bool live = task < ntask;
+      const int n2 = task % 8, pair = live ? (task / 8) % npair : 0, q = live ? task / (8 * npair) : 0;
+      float2* za = lds + q * W::TS + W::place(inverse(2 * pair)) * RS;
+      float2* zb = lds + q * W::TS + W::place(inverse(2 * pair + 1)) * RS;
+      const bool has1 = 2 * pair + 1 < KR;
+      float re[N1], im[N1];
+      if (live) {
+#pragma unroll
+        for (int i = 0; i < N1 / 2; ++i) {
+          const int v = 8 * i + n2, m = H2 - v;  // element v, and element L/2 + v from bin m
+          float2 a = za[v], b = has1 ? zb[v] : make_float2(0.f, 0.f);
+          const bool first = v == 0;  // bins 0 and L/2 are the parts of slot 0
+          re[i] = first ? a.x : a.x - b.y;
+          im[i] = first ? b.x : a.y + b.x;
+          const float2 c = za[first ? 0 : m], d = has1 ? zb[first ? 0 : m] : make_float2(0.f, 0.f);
+          re[N1 / 2 + i] = first ? a.y : c.x + d.y;
+          im[N1 / 2 + i] = first ? b.y : d.x - c.y;
+        }
+        fft_dif<N1, +1, false>(re, im);
+      }
+      __syncthreads();
+      if (live) {
+#pragma unroll
+        for (int k = 0; k < N1 / 2; ++k) {
+          za[8 * k + n2] = turned<L, +1>(tw, n2, k, re[bitrev(k, N1)], im[bitrev(k, N1)]);
+          zb[8 * k + n2] = turned<L, +1>(tw, n2, k + N1 / 2, re[bitrev(k + N1 / 2, N1)], im[bitrev(k + N1 / 2, N1)]);
+        }
+      }
+    }
+    __syncthreads();
+    // row pairs, 8 points
+    for (int task = tid; task < nq * npair * N1; task += nthr) {
+      const int pair = task % npair, k1 = (task / npair) % N1, q = task / (npair * N1);
+      const int row = inverse(2 * pair + (k1 < N1 / 2 ? 0 : 1));
+      pass8<+1>(lds + q * W::TS + W::place(row) * RS + 8 * (k1 % (N1 / 2)), 1);
+    }
+    __syncthreads();
+    // real element at kept row a, kept column c of tile q, unscaled
+    auto row_base = [&](int q, int a, int& second) {
+      second = (W::place(inverse(a | 1)) - W::place(inverse(a & ~1))) * RS * 2;
+      return (q * W::TS + W::place(inverse(a & ~1)) * RS) * 2 + (a & 1);
+    };
+    auto at = [&](int rb, int second, int c) {
+      const int pos = W::place(inverse(c));
+      return ldf[rb + (pos < H2 ? 2 * pos : second + 2 * (pos - H2))];
+    };
+    const int H = p.H, lane = tid & 63, wave = tid >> 6, nwave = nthr >> 6;
+    if (MODE == 3) {
+      // rows and columns of the block inside the plane: a wave per row
+      const int img = t0 / P, b = p.pitch, i0 = Pb * b - p.off, j0 = Qb * b - p.off;
+      float* out = p.dst + (size_t(img) * p.n_ch + ch) * H * H;
+      for (int r = max(0, -i0) + wave; r < min(b, H - i0); r += nwave) {
+        for (int c = max(0, -j0) + lane; c < min(b, H - j0); c += 64) {
+          float acc = 0.f;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int a = q / 2 ? r : r + b, cc = q % 2 ? c : c + b;
+            if (!has(q) || a >= KR || cc >= KR) continue;
+            int second;
+            const int rb = row_base(q, a, second);
+            acc += at(rb, second, cc);
+          }
+          out[size_t(i0 + r) * H + j0 + c] = acc * scale;
+        }
+      }
+    } else if (MODE == 1) {
+      // plane = group: a wave per output row, lanes over the columns
+      const int img = t0 / P, T = p.T, b = p.pitch;
+      float* out = p.dst + (size_t(img) * p.n_ch + ch) * H * H;
+      const SmallDiv div_b(b);
+      for (int i = wave; i < H; i += nwave) {
+        const int a = i + p.off, P1 = div_b(a), ra1 = a - P1 * b;
+        const bool r1 = P1 < T, r0 = P1 >= 1 && P1 - 1 < T && ra1 + b < KR;
+        for (int jx = lane; jx < H; jx += 64) {
+          const int c = jx + p.off, Q1 = div_b(c), ca1 = c - Q1 * b;
+          const bool c1 = Q1 < T, c0 = Q1 >= 1 && Q1 - 1 < T && ca1 + b < KR;
+          float acc = 0.f;
+          auto add = [&](bool on, int Pt, int Qt, int ra, int ca) {
+            if (!on) return;
+            int second;
+            const int rb = row_base(Pt * T + Qt, ra, second);
+            acc += at(rb, second, ca);
+          };
+          add(r0 && c0, P1 - 1, Q1 - 1, ra1 + b, ca1 + b);
+          add(r0 && c1, P1 - 1, Q1, ra1 + b, ca1);
+          add(r1 && c0, P1, Q1 - 1, ra1, ca1 + b);
+          add(r1 && c1, P1, Q1, ra1, ca1);
+          out[size_t(i) * H + jx] = acc * scale;
+        }
+      }
+    } else {
+      // a wave per kept row of a tile, lanes over its columns
+      for (int r = wave; r < nq * KR; r += nwave) {
+        const int q = r / KR, a = r - q * KR, t = t0 + q;
+        int second;
+        const int rb = row_base(q, a, second);
+        if (MODE == 2) {
+          float* ot = p.tiles + ((size_t(ch) * tpc + t) * KR + a) * KR;
+          for (int c = lane; c < KR; c += 64) ot[c] = at(rb, second, c) * scale;
+        } else {
+          const int img = t / P, pp = t - img * P, pr = pp / p.T, qc = pp - pr * p.T;
+          if (pr * p.pitch + a >= H) continue;
+          const int ncol = min(KR, H - qc * p.pitch);
+          float* orow = p.dst + ((size_t(img) * p.n_ch + ch) * H + pr * p.pitch + a) * H + qc * p.pitch;
+          for (int c = lane; c < ncol; c += 64) orow[c] = at(rb, second, c) * scale;
+        }
+      }
+    }
+    __syncthreads();
+  }
+}
+
+// ---------------------------------------------------------------------------
+// launchers
+
+template <int L>
+constexpr size_t wide_lds(int TQ) { return (size_t(Wide<L>::TS) * TQ + L) * 8; }
+
+// Threads: one N1-point task each, up to a whole workgroup.
+template <int L>
+int wide_threads(int TQ) { return std::min(kWideMaxThreads, Wide<L>::TASKS * TQ); }
+
+// Persistent grid: as many workgroups as are resident (by LDS; two of 512 or
+// one of 1024 lanes by registers), whole rounds over the 8 XCDs.
+template <int L>
+unsigned wide_grid(long ngroups, int TQ) {
+  const long per_cu = std::max<long>(1, std::min<long>(long(kWideLds / wide_lds<L>(TQ)), 1024 / wide_threads<L>(TQ)));
+  return unsigned(std::max<long>(8, std::min<long>(per_cu * device_cus(), (ngroups + 7) / 8 * 8) / 8 * 8));
+}
+
+// Tiles per group: one while they are at most one per CU, then two, which
+// doubles the runs of a bin (16 bytes). Measured: forward at L = 128, 400
+// tiles 28 us one by one and 22 in pairs, 16384 tiles 1.91 and 1.08 ms;
+// inverse 400 tiles 33 and 27 us, but 4096 tiles 0.36 and 0.41 ms (a pair
+// leaves one workgroup per CU).
+int wide_tiles(long tiles, long tpc, bool inverse) {
+  return tpc < 2 || tiles <= device_cus() || (inverse && tiles > 1536) ? 1 : 2;
+}
+
+template <int L>
+hipError_t launch_fwd(BigFwdParams p, hipStream_t s) {
+  const long tpc = long(p.n_img) * p.T * p.T;
+  p.TQ = wide_tiles(tpc * p.n_ch, tpc, false);
+  p.ngrp = int((tpc + p.TQ - 1) / p.TQ);
+  auto kern = wide_rfft2_kernel<L>;
+  const hipError_t e = allow_lds(kern, kWideLds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3(wide_grid<L>(long(p.n_ch) * p.ngrp, p.TQ)), dim3(wide_threads<L>(p.TQ)),
+                     wide_lds<L>(p.TQ), s, p);
+  return hipGetLastError();
+}
+
+template <int L, int MODE>
+hipError_t launch_inv_mode(BigInvParams p, hipStream_t s) {
+  const long tpc = long(p.n_img) * p.T * p.T;
+  p.TQ = MODE == 1 ? p.T * p.T : MODE == 3 ? 4 : wide_tiles(tpc * p.n_ch, tpc, true);
+  p.To = MODE == 3 ? (p.H + p.off + p.pitch - 1) / p.pitch : 0;
+  const long groups = MODE == 3 ? long(p.n_img) * p.To * p.To : (tpc + p.TQ - 1) / p.TQ;
+  if (groups > 0x7fffffffL || (MODE == 3 && (p.To < p.T || p.KR > 2 * p.pitch))) return hipErrorInvalidValue;
+  p.ngrp = int(groups);
+  if (wide_lds<L>(p.TQ) > kWideLds) return hipErrorInvalidConfiguration;
+  auto kern = wide_irfft2_kernel<L, MODE>;
+  const hipError_t e = allow_lds(kern, kWideLds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3(wide_grid<L>(long(p.n_ch) * p.ngrp, p.TQ)), dim3(wide_threads<L>(p.TQ)),
+                     wide_lds<L>(p.TQ), s, p);
+  return hipGetLastError();
+}
+
+template <int L>
+hipError_t launch_inv(const BigInvParams& p, hipStream_t s) {
+  switch (p.overlap) {
+    case 0: return launch_inv_mode<L, 0>(p, s);
+    case 1: return launch_inv_mode<L, 1>(p, s);
+    case 2: return launch_inv_mode<L, 2>(p, s);
+    case 3:
+      if constexpr (L == 64) return launch_inv_mode<L, 3>(p, s);
+      return hipErrorInvalidValue;
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace
+
+hipError_t launch_wide_rfft2(int L, const BigFwdParams& p, hipStream_t s) {
+  return L == 64 ? launch_fwd<64>(p, s) : L == 128 ? launch_fwd<128>(p, s) : hipErrorInvalidValue;
+}
+
+hipError_t launch_wide_irfft2(int L, const BigInvParams& p, hipStream_t s) {
+  return L == 64 ? launch_inv<64>(p, s) : L == 128 ? launch_inv<128>(p, s) : hipErrorInvalidValue;
+}
+
+}  // namespace oaa

@@ -156,13 +156,23 @@ struct BigInvParams {
   int n_img, n_ch;
   int H, pitch, off, T;
   int KR, rot, overlap;
-  int TQ, ngrp;       // launcher
+  int TQ, ngrp, To;   // launcher
 };
 hipError_t launch_big_rfft2(int L, const BigFwdParams& p, hipStream_t s);
+// The same transforms on kernels that spread each over lanes (k_wide_fft.hip):
+// launch_big_* check the parameters and choose.
+hipError_t launch_wide_rfft2(int L, const BigFwdParams& p, hipStream_t s);
+hipError_t launch_wide_irfft2(int L, const BigInvParams& p, hipStream_t s);
+// Compute units of the current device.
+int device_cus();
 hipError_t launch_big_irfft2(int L, const BigInvParams& p, hipStream_t s);
 // Whether launch_big_irfft2 overlap-adds planes of T x T tiles in one
 // workgroup (else it needs the `tiles` scratch).
 bool big_overlap_supported(int L, int T);
+// Whether n_planes planes of T x T tiles of side L, which do not fit one
+// workgroup, are few enough for launch_big_irfft2 to overlap-add them block by
+// block without the scratch.
+bool big_overlap_few(int L, long n_planes, int T);
 // Bytes of that scratch for n_planes planes of T x T tiles keeping KR x KR.
 inline size_t overlap_tile_bytes(long n_planes, int T, int KR) {
   return size_t(n_planes) * T * T * KR * KR * 4;

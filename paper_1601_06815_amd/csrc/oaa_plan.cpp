@@ -577,7 +577,8 @@ oaa_status_t forward_pass(const Ctx& cx, const float* x, const float* w, float* 
     return big_inverse(cx, OAA_STAGE_FWD_INVERSE, "inverse transform + overlap-save crop",
                        region(cx, OAA_REGION_PRODUCT), 1, 0, y, p->B, p->K, p->M, p->b, 0, p->T, p->b,
                        (p->L - (p->n - 1)) & (p->L - 1), false);
-  if (big_side(p) && (oaa::big_overlap_supported(p->L, p->T) || p->L >= OAA_TWO_STEP_MIN_L))
+  if (big_side(p) && (oaa::big_overlap_supported(p->L, p->T) || p->L >= OAA_TWO_STEP_MIN_L ||
+                      oaa::big_overlap_few(p->L, long(p->B) * p->K, p->T)))
     return big_inverse(cx, OAA_STAGE_FWD_INVERSE, "inverse transform + overlap-add", region(cx, OAA_REGION_PRODUCT),
                        1, 0, y, p->B, p->K, p->M, p->b, p->n - 1, p->T, p->b + p->n - 1, 0, true);
   if (p->method == OAA_METHOD_OVERLAP_SAVE) {
@@ -642,7 +643,8 @@ oaa_status_t backward_data_pass(const Ctx& cx, const float* g, const float* w, f
   if (big_side(p) && p->method != OAA_METHOD_OVERLAP_SAVE)
     return big_inverse(cx, OAA_STAGE_BWD_DATA_INVERSE, "inverse transform + block crop", region(cx, OAA_REGION_PRODUCT),
                        1, 0, dx, p->B, p->C, p->N, p->b, 0, p->T, p->b, 0, false);
-  if (big_side(p) && (oaa::big_overlap_supported(p->L, p->T) || p->L >= OAA_TWO_STEP_MIN_L))
+  if (big_side(p) && (oaa::big_overlap_supported(p->L, p->T) || p->L >= OAA_TWO_STEP_MIN_L ||
+                      oaa::big_overlap_few(p->L, long(p->B) * p->C, p->T)))
     return big_inverse(cx, OAA_STAGE_BWD_DATA_INVERSE, "inverse transform + overlap-add",
                        region(cx, OAA_REGION_PRODUCT), 1, 0, dx, p->B, p->C, p->N, p->b, 0, p->T, p->L, p->n - 1, true);
   if (p->method == OAA_METHOD_OVERLAP_SAVE) {

@@ -687,6 +687,27 @@ def test_kernel_chain_two_stacked_layers(gpu_lib, shape):
     assert max(e) <= TOL, e
 
 
+@pytest.mark.parametrize("shape", [
+    (1, 1, 1, 224, 8, 64, 57, "oaa"),     # 16 blocks of one plane, each on its own
+    (1, 2, 7, 200, 20, 64, 45, "oaa"),    # 5 x 5 blocks, ragged
+    (1, 1, 3, 150, 17, 64, 30, "oaa"),    # the same with blocks of less than half a tile
+    (1, 3, 2, 224, 10, 64, 0, "oas"),     # the same for the error propagation, one block more per side
+    (1, 2, 20, 150, 20, 64, 45, "oaa"),   # 320 tiles: a workgroup per block row again
+    (2, 9, 40, 41, 24, 64, 41, "oaa"),    # 360 kernel tiles: pairs; planes of one tile
+    (3, 5, 61, 40, 24, 64, 41, "oaa"),    # odd numbers of tiles per channel
+    (1, 5, 60, 66, 40, 128, 89, "oaa"),   # side 128: 300 kernel tiles in pairs, single data tiles
+    (3, 3, 5, 200, 50, 128, 79, "oaa"),   # 3 x 3 tiles of side 128 through the scratch
+    (2, 3, 40, 200, 50, 128, 0, "oas"),   # overlap-save at side 128
+], ids=lambda s: "x".join(map(str, s)))
+def test_transforms_spread_over_lanes(gpu_lib, shape):
+    """Large sides in launches of few tiles, over the tiles per workgroup and
+    the output modes of the kernels, against the oracle."""
+    B, C, K, N, n, L, b, method = shape
+    x, w, g = make_inputs(Layer("t", B, C, K, N, n), seed=43 + sum(shape[:7]))
+    check_whole(x, w, g, tiling=(L, b),
+                method=binding.METHOD_OVERLAP_SAVE if method == "oas" else binding.METHOD_OVERLAP_ADD)
+
+
 def test_stage_spectra_match_oracle_steps(gpu_lib):
     """Workspace spectra (kernel, input blocks, gradient windows, products)
     against the OaA steps of the oracle, in the layouts oaa.h documents."""
