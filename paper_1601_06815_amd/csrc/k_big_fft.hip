@@ -604,14 +604,8 @@ hipError_t launch_big_fwd(int L, BigFwdParams p, hipStream_t s) {
   const int P = p.T * p.T;
   const long tpc = long(p.n_img) * P;
   if (tpc < 1 || tpc > 0x7fffffffL) return hipErrorInvalidValue;
-  if (p.run == 0) {
-    p.run = int(tpc);
-    p.rs = 0;
-    p.bs = size_t(p.n_ch) * size_t(tpc);
-    p.cs = size_t(tpc);
-  }
   if (p.run < 1) return hipErrorInvalidValue;
-  if (L != Big::L || tpc * p.n_ch <= kWideFwdTiles) return launch_wide_rfft2(L, p, s);
+  if (L != Big::L || tpc * p.n_ch <= kWideFwdTiles) return launch_wide_rfft2(L, p, nullptr, s);
   p.TQ = group_tiles(P, tpc);
   p.ngrp = int((tpc + p.TQ - 1) / p.TQ);
   // one past the largest element the layout addresses

@@ -122,8 +122,8 @@ struct GemmParams {
 // pitch = S = H (tile t = kernel t).
 //
 // dst layout: element (bin f, ch, tile t) at f bs + ch cs + (t / run) rs +
-// t % run. run = 0 (the launcher's default) is [F][n_ch][n_img T T]; the
-// fused few-channel passes use runs of the T blocks of a block row
+// t % run. run = n_img T T, cs = run, bs = n_ch run is [F][n_ch][n_img T T];
+// the fused few-channel passes use runs of the T blocks of a block row
 // (run = T, rs = n_ch F T, bs = T, cs = F T) and of four kernels.
 struct BigFwdParams {
   const float* src;  // [n_img][n_ch][H][H]
@@ -161,8 +161,32 @@ struct BigInvParams {
 hipError_t launch_big_rfft2(int L, const BigFwdParams& p, hipStream_t s);
 // The same transforms on kernels that spread each over lanes (k_wide_fft.hip):
 // launch_big_* check the parameters and choose.
-hipError_t launch_wide_rfft2(int L, const BigFwdParams& p, hipStream_t s);
+hipError_t launch_wide_rfft2(int L, const BigFwdParams& a, const BigFwdParams* b, hipStream_t s);
 hipError_t launch_wide_irfft2(int L, const BigInvParams& p, hipStream_t s);
+// Whether one launch of them should do two forward jobs (L = 16 to 128; with
+// per-stage timing they run apart): each
+// job alone lasts about as long as a launch takes. Measured at L = 16: 4.1 us
+// for 12 kernel tiles, 4.5 for 147 input tiles, 4.2 for both; at L = 32 7.2 and
+// 6.6 (on the kernels of many tiles), 4.3.
+bool wide_pair_fits(int L, long tiles_a, int Ha, long tiles_b, int Hb);
+// Whether L = 32 (whose other kernels hold a sequence per lane) takes them, for
+// `tiles` tiles of planes of side H, T per side. Measured, in us, the other
+// kernels first:
+//  * kernels: 9 tiles 7.2 / 4.2, 513 tiles 7.2 / 5.3, 3072 tiles 9.0 / 9.7;
+//  * blocks (rows of under 16, not exactly half a transform): 49 tiles 6.6 /
+//    4.3, 6912 tiles 32 / 17, 26400 tiles 53 / 49, 147456 tiles 671 / 268;
+//  * windows: 441 tiles 14.6 / 4.9, 1215 tiles 9.5 / 6.5, 9216 tiles 20.7 /
+//    23.4, 59664 tiles (T = 4, whose rows fill lines) 88 / 113, 147456 tiles
+//    (T = 3) 450 / 267.
+enum class WideUse { kernels, blocks, windows };
+bool wide_takes(int L, WideUse use, long tiles, int T, int H);
+// How L = 32 should overlap-add n_planes planes of T x T tiles with blocks b
+// on them: 0 not, 1 a plane per workgroup, 3 a block per workgroup (the overlap
+// of BigInvParams). Measured, in us, the other kernels first: 240 tiles (T = 2)
+// 10.9 / 7.0 by planes / 6.4 by blocks, 441 tiles 9.7 / - / 8.1, 135 planes of
+// nine tiles 12.6 / 8.9 / 19.6, 1024 planes 44 / 33, 3729 planes (T = 4) 304 /
+// 194, 4096 planes of nine 124 / 123, 16384 planes 459 / 577.
+int wide_overlap(int L, long n_planes, int T, int b);
 // Compute units of the current device.
 int device_cus();
 hipError_t launch_big_irfft2(int L, const BigInvParams& p, hipStream_t s);

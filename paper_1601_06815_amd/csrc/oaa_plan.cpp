@@ -198,14 +198,14 @@ bool big_side(const oaa_plan_s* p) { return p->L >= OAA_BIG_MIN_L; }
 
 // Forward transform of S x S windows starting every `pitch` at -off in the
 // H x H planes of src (n_img x n_ch of them, T x T windows each) into `dst`.
-oaa_status_t big_forward(const Ctx& cx, oaa_stage_t stage, const char* what, const float* src, float2* dst,
-                         int n_img, int n_ch, int H, int pitch, int off, int S, int T, int run = 0, size_t bs = 0,
-                         size_t cs = 0, size_t rs = 0) {
+oaa::BigFwdParams forward_job(const float* src, float2* dst, int n_img, int n_ch, int H, int pitch, int off, int S,
+                              int T, int run = 0, size_t bs = 0, size_t cs = 0, size_t rs = 0) {
+  const size_t tpc = size_t(n_img) * T * T;
   oaa::BigFwdParams b{};
-  b.run = run;
-  b.bs = bs;
-  b.cs = cs;
-  b.rs = rs;
+  b.run = run ? run : int(tpc);
+  b.bs = run ? bs : size_t(n_ch) * tpc;
+  b.cs = run ? cs : tpc;
+  b.rs = run ? rs : 0;
   b.src = src;
   b.dst = dst;
   b.n_img = n_img;
@@ -215,18 +215,69 @@ oaa_status_t big_forward(const Ctx& cx, oaa_stage_t stage, const char* what, con
   b.off = off;
   b.S = S;
   b.T = T;
-  return timed(cx, stage, what, [&] { return oaa::launch_big_rfft2(cx.p->L, b, cx.s); });
+  return b;
+}
+
+long job_tiles(const oaa::BigFwdParams& b) { return long(b.n_img) * b.n_ch * b.T * b.T; }
+
+// Kernels w [K][C][n][n] as single-tile planes, into the unfused layout
+// [F][C][K].
+oaa::BigFwdParams kernel_job(const float* w, int K, int C, int n, float2* dst) {
+  return forward_job(w, dst, K, C, n, n, 0, n, 1);
+}
+
+// The plan's kernel and input spectra as such jobs, in its layouts.
+oaa::BigFwdParams kernel_job(const Ctx& cx, const float* w) {
+  const oaa_plan_s* p = cx.p;
+  float2* dst = region(cx, OAA_REGION_W_SPECTRUM);
+  if (!p->fused) return kernel_job(w, p->K, p->C, p->n, dst);
+  // kernel by kernel, bins contiguous: (f, c, k) at (k C + c) F + f
+  const size_t F = p->F, C = p->C;
+  return forward_job(w, dst, p->K, p->C, p->n, p->n, 0, p->n, 1, 1, 1, F, C * F);
+}
+
+oaa::BigFwdParams input_job(const Ctx& cx, const float* x) {
+  const oaa_plan_s* p = cx.p;
+  float2* dst = region(cx, OAA_REGION_X_SPECTRUM);
+  // overlap-save: L x L windows every h; overlap-add: b x b blocks
+  const int S = p->method == OAA_METHOD_OVERLAP_SAVE ? p->L : p->b;
+  if (!p->fused) return forward_job(x, dst, p->B, p->C, p->N, p->b, 0, S, p->T);
+  // runs of a block row: (f, c, block (P, Q) of img) at ((img T + P) C + c) F T + f T + Q
+  const size_t F = p->F, C = p->C, T = p->T;
+  return forward_job(x, dst, p->B, p->C, p->N, p->b, 0, S, p->T, p->T, T, F * T, C * F * T);
+}
+
+// A job on the kernels of large sides (or of few tiles at L = 32).
+oaa_status_t run_job(const Ctx& cx, oaa_stage_t stage, const char* what, const oaa::BigFwdParams& job) {
+  return timed(cx, stage, what, [&] {
+    return cx.p->L >= OAA_BIG_MIN_L ? oaa::launch_big_rfft2(cx.p->L, job, cx.s)
+                                    : oaa::launch_wide_rfft2(cx.p->L, job, nullptr, cx.s);
+  });
+}
+
+// Whether two jobs go through one launch. The kernels of that launch then take
+// each of them alone too (per-stage timing, cached spectra), so that spectra
+// do not depend on which calls computed them.
+bool pair_fits(const oaa_plan_s* p, const oaa::BigFwdParams& a, const oaa::BigFwdParams& b) {
+  return oaa::wide_pair_fits(p->L, job_tiles(a), a.H, job_tiles(b), b.H);
+}
+
+// The same for the plan's kernel and input spectra.
+bool inputs_pair(const Ctx& cx) { return pair_fits(cx.p, kernel_job(cx, nullptr), input_job(cx, nullptr)); }
+
+oaa_status_t run_pair(const Ctx& cx, const oaa::BigFwdParams& a, const oaa::BigFwdParams& b) {
+  return hip_status(oaa::launch_wide_rfft2(cx.p->L, a, &b, cx.s), "two forward transforms");
 }
 
 // Inverse transform of the spectra at src (nsplit partial sums spaced
 // split_stride apart) of n_img x n_ch planes of T x T tiles; row and column r
 // of each inverse become index (r + rot) mod L, of which [0, KR) are kept and
 // either written to block (P, Q) at (P pitch, Q pitch) of the H x H output
-// planes (overlap false) or overlap-added there, pixel (i, j) being framed
-// pixel (i + off, j + off) (overlap true).
+// planes (overlap 0) or overlap-added there, pixel (i, j) being framed pixel
+// (i + off, j + off) (overlap 1; at L = 32 also 3, see wide_overlap).
 oaa_status_t big_inverse(const Ctx& cx, oaa_stage_t stage, const char* what, const float2* src, int nsplit,
                          size_t split_stride, float* dst, int n_img, int n_ch, int H, int pitch, int off, int T, int KR,
-                         int rot, bool overlap) {
+                         int rot, int overlap) {
   oaa::BigInvParams b{};
   b.src = src;
   b.nsplit = nsplit;
@@ -241,46 +292,39 @@ oaa_status_t big_inverse(const Ctx& cx, oaa_stage_t stage, const char* what, con
   b.T = T;
   b.KR = KR;
   b.rot = rot;
-  b.overlap = overlap ? 1 : 0;
-  return timed(cx, stage, what, [&] { return oaa::launch_big_irfft2(cx.p->L, b, cx.s); });
+  b.overlap = overlap;
+  return timed(cx, stage, what, [&] {
+    return cx.p->L >= OAA_BIG_MIN_L ? oaa::launch_big_irfft2(cx.p->L, b, cx.s)
+                                    : oaa::launch_wide_irfft2(cx.p->L, b, cx.s);
+  });
 }
 
-oaa_status_t filter_spectra(const Ctx& cx, const float* w, int K, int C, int n, float2* dst);
-
-oaa_status_t run_filter_fft(const Ctx& cx, const float* w) {
-  oaa_plan_t p = cx.p;
-  if (p->fused) {
-    // kernel by kernel, bins contiguous: (f, c, k) at (k C + c) F + f
-    const size_t F = p->F, C = p->C;
-    oaa_status_t st = big_forward(cx, OAA_STAGE_W_SPECTRUM, "kernel spectra", w, region(cx, OAA_REGION_W_SPECTRUM),
-                                  p->K, p->C, p->n, p->n, 0, p->n, 1, 1, 1, F, C * F);
-    if (st == OAA_OK && cx.own) p->w_valid = true;
-    return st;
-  }
-  oaa_status_t st = filter_spectra(cx, w, p->K, p->C, p->n, region(cx, OAA_REGION_W_SPECTRUM));
-  if (st == OAA_OK && cx.own) p->w_valid = true;
-  return st;
-}
-
-// Spectra [F][C][K] at the plan's L of K x C kernels w[k][c] of side n
-// (n <= L), zero-padded: the unfused kernel-spectra layout.
-oaa_status_t filter_spectra(const Ctx& cx, const float* w, int K, int C, int n, float2* dst) {
+// Spectra at the plan's L of the K x C kernels of `job` (side job.H <= L,
+// zero-padded); `paired`: one of two jobs that fit one launch.
+oaa_status_t filter_spectra(const Ctx& cx, const oaa::BigFwdParams& job, bool paired) {
   oaa_plan_t p = cx.p;
   hipStream_t s = cx.s;
-  if (big_side(p))  // kernels as single-tile planes w[k][c]
-    return big_forward(cx, OAA_STAGE_W_SPECTRUM, "kernel spectra", w, dst, K, C, n, n, 0, n, 1);
+  const char* what = "kernel spectra";
+  if (big_side(p) || paired || oaa::wide_takes(p->L, oaa::WideUse::kernels, job_tiles(job), 1, job.H))
+    return run_job(cx, OAA_STAGE_W_SPECTRUM, what, job);
   oaa::TileFwdParams t{};
-  t.src = w;
-  t.dst = dst;
-  t.n_img = K;
-  t.n_ch = C;
-  t.H = n;
-  t.pitch = n;
+  t.src = job.src;
+  t.dst = job.dst;
+  t.n_img = job.n_img;
+  t.n_ch = job.n_ch;
+  t.H = job.H;
+  t.pitch = job.H;
   t.off = 0;
-  t.R = n;
+  t.R = job.H;
   t.T = 1;
   t.gather = 1;
-  return timed(cx, OAA_STAGE_W_SPECTRUM, "kernel spectra", [&] { return oaa::launch_tile_rfft2(p->L, t, s); });
+  return timed(cx, OAA_STAGE_W_SPECTRUM, what, [&] { return oaa::launch_tile_rfft2(p->L, t, s); });
+}
+
+oaa_status_t run_filter_fft(const Ctx& cx, const float* w) {
+  const oaa_status_t st = filter_spectra(cx, kernel_job(cx, w), inputs_pair(cx));
+  if (st == OAA_OK && cx.own) cx.p->w_valid = true;
+  return st;
 }
 
 // Scratch of the two layers' spectra for kernel_chain: W1hat [F][C][J], then
@@ -300,8 +344,14 @@ oaa_status_t kernel_chain(const Ctx& cx, const float* w1, int J, int n1, const f
   oaa_plan_t p = cx.p;
   float2* w1h = reinterpret_cast<float2*>(scratch);
   float2* w2h = reinterpret_cast<float2*>(scratch + align_up(size_t(p->F) * p->C * J * 8));
-  if (oaa_status_t st = filter_spectra(cx, w1, J, p->C, n1, w1h)) return st;
-  if (oaa_status_t st = filter_spectra(cx, w2, p->K, J, n2, w2h)) return st;
+  const oaa::BigFwdParams j1 = kernel_job(w1, J, p->C, n1, w1h), j2 = kernel_job(w2, p->K, J, n2, w2h);
+  const bool paired = pair_fits(p, j1, j2);
+  if (paired && !cx.p->timing) {
+    if (oaa_status_t st = run_pair(cx, j1, j2)) return st;
+  } else {
+    if (oaa_status_t st = filter_spectra(cx, j1, paired)) return st;
+    if (oaa_status_t st = filter_spectra(cx, j2, paired)) return st;
+  }
   oaa::GemmParams g{};
   g.A = w1h;
   g.B = w2h;
@@ -325,25 +375,16 @@ oaa_status_t kernel_chain(const Ctx& cx, const float* w1, int J, int n1, const f
 oaa_status_t run_input_fft(const Ctx& cx, const float* x) {
   oaa_plan_t p = cx.p;
   hipStream_t s = cx.s;
-  if (p->fused) {
-    // runs of a block row: (f, c, block (P, Q) of img) at ((img T + P) C + c) F T + f T + Q
-    const size_t F = p->F, C = p->C, T = p->T;
-    oaa_status_t st = big_forward(cx, OAA_STAGE_X_SPECTRUM, "input block spectra", x,
-                                  region(cx, OAA_REGION_X_SPECTRUM), p->B, p->C, p->N, p->b, 0, p->b, p->T, p->T, T,
-                                  F * T, C * F * T);
+  const bool oas = p->method == OAA_METHOD_OVERLAP_SAVE;
+  const oaa::BigFwdParams job = input_job(cx, x);
+  const oaa::WideUse use = oas || (2 * p->b == p->L && p->T < 16) ? oaa::WideUse::windows : oaa::WideUse::blocks;
+  if (big_side(p) || inputs_pair(cx) || oaa::wide_takes(p->L, use, job_tiles(job), p->T, p->N)) {
+    oaa_status_t st =
+        run_job(cx, OAA_STAGE_X_SPECTRUM, oas ? "input window spectra" : "input block spectra", job);
     if (st == OAA_OK && cx.own) p->x_valid = true;
     return st;
   }
-  if (big_side(p)) {
-    // overlap-save: L x L windows every h; overlap-add: b x b blocks
-    const bool oas = p->method == OAA_METHOD_OVERLAP_SAVE;
-    oaa_status_t st = big_forward(cx, OAA_STAGE_X_SPECTRUM, oas ? "input window spectra" : "input block spectra", x,
-                                  region(cx, OAA_REGION_X_SPECTRUM), p->B, p->C, p->N, p->b, 0, oas ? p->L : p->b,
-                                  p->T);
-    if (st == OAA_OK && cx.own) p->x_valid = true;
-    return st;
-  }
-  if (p->method == OAA_METHOD_OVERLAP_SAVE) {
+  if (oas) {
     // L x L windows of x starting every h = L - n + 1
     oaa::WindowParams t{};
     t.src = x;
@@ -396,13 +437,16 @@ oaa_status_t run_input_fft(const Ctx& cx, const float* x) {
 oaa_status_t run_grad_fft(const Ctx& cx, const float* g) {
   oaa_plan_t p = cx.p;
   hipStream_t s = cx.s;
-  if (big_side(p)) {
-    // overlap-save: h x h blocks of g; overlap-add: windows of side
-    // min(2b, L) of the gradient framed by n - 1 zeros, every b
-    const bool oas = p->method == OAA_METHOD_OVERLAP_SAVE;
-    oaa_status_t st = big_forward(cx, OAA_STAGE_G_SPECTRUM, oas ? "gradient block spectra" : "gradient window spectra",
-                                  g, region(cx, OAA_REGION_G_SPECTRUM), p->B, p->K, p->M, p->b,
-                                  oas ? 0 : p->n - 1, oas ? p->b : std::min(2 * p->b, p->L), p->T);
+  // overlap-save: h x h blocks of g; overlap-add: windows of side min(2b, L)
+  // of the gradient framed by n - 1 zeros, every b
+  const bool oas = p->method == OAA_METHOD_OVERLAP_SAVE;
+  const oaa::BigFwdParams job =
+      forward_job(g, region(cx, OAA_REGION_G_SPECTRUM), p->B, p->K, p->M, p->b, oas ? 0 : p->n - 1,
+                  oas ? p->b : std::min(2 * p->b, p->L), p->T);
+  const oaa::WideUse use = oas && !(2 * p->b == p->L && p->T < 16) ? oaa::WideUse::blocks : oaa::WideUse::windows;
+  if (big_side(p) || oaa::wide_takes(p->L, use, job_tiles(job), p->T, p->M)) {
+    oaa_status_t st =
+        run_job(cx, OAA_STAGE_G_SPECTRUM, oas ? "gradient block spectra" : "gradient window spectra", job);
     if (st == OAA_OK && cx.own) p->g_valid = true;
     return st;
   }
@@ -547,8 +591,13 @@ oaa_status_t forward_pass(const Ctx& cx, const float* x, const float* w, float* 
   oaa_plan_t p = cx.p;
   hipStream_t s = cx.s;
   oaa_status_t st;
-  if (w && (st = run_filter_fft(cx, w))) return st;
-  if ((st = run_input_fft(cx, x))) return st;
+  if (w && inputs_pair(cx) && !(cx.own && p->timing)) {
+    if ((st = run_pair(cx, kernel_job(cx, w), input_job(cx, x)))) return st;
+    if (cx.own) p->w_valid = p->x_valid = true;
+  } else {
+    if (w && (st = run_filter_fft(cx, w))) return st;
+    if ((st = run_input_fft(cx, x))) return st;
+  }
   if (p->fused) {
     oaa::FusedFwdParams f{};
     f.xs = region(cx, OAA_REGION_X_SPECTRUM);
@@ -576,11 +625,11 @@ oaa_status_t forward_pass(const Ctx& cx, const float* x, const float* w, float* 
   if (big_side(p) && p->method == OAA_METHOD_OVERLAP_SAVE)
     return big_inverse(cx, OAA_STAGE_FWD_INVERSE, "inverse transform + overlap-save crop",
                        region(cx, OAA_REGION_PRODUCT), 1, 0, y, p->B, p->K, p->M, p->b, 0, p->T, p->b,
-                       (p->L - (p->n - 1)) & (p->L - 1), false);
+                       (p->L - (p->n - 1)) & (p->L - 1), 0);
   if (big_side(p) && (oaa::big_overlap_supported(p->L, p->T) || p->L >= OAA_TWO_STEP_MIN_L ||
                       oaa::big_overlap_few(p->L, long(p->B) * p->K, p->T)))
     return big_inverse(cx, OAA_STAGE_FWD_INVERSE, "inverse transform + overlap-add", region(cx, OAA_REGION_PRODUCT),
-                       1, 0, y, p->B, p->K, p->M, p->b, p->n - 1, p->T, p->b + p->n - 1, 0, true);
+                       1, 0, y, p->B, p->K, p->M, p->b, p->n - 1, p->T, p->b + p->n - 1, 0, 1);
   if (p->method == OAA_METHOD_OVERLAP_SAVE) {
     // rows and columns [n-1, L) of each window's inverse are its h x h outputs
     oaa::CropParams c{};
@@ -593,6 +642,9 @@ oaa_status_t forward_pass(const Ctx& cx, const float* x, const float* w, float* 
     return timed(cx, OAA_STAGE_FWD_INVERSE, "inverse transform + overlap-save crop",
                  [&] { return oaa::launch_irfft2_crop(p->L, c, s); });
   }
+  if (const int how = oaa::wide_overlap(p->L, long(p->B) * p->K, p->T, p->b))
+    return big_inverse(cx, OAA_STAGE_FWD_INVERSE, "inverse transform + overlap-add", region(cx, OAA_REGION_PRODUCT),
+                       1, 0, y, p->B, p->K, p->M, p->b, p->n - 1, p->T, p->b + p->n - 1, 0, how);
   oaa::FoldCropParams o{};
   o.src = region(cx, OAA_REGION_PRODUCT);
   o.dst = y;
@@ -642,16 +694,20 @@ oaa_status_t backward_data_pass(const Ctx& cx, const float* g, const float* w, f
   if ((st = run_gemm(cx, gm, OAA_STAGE_BWD_DATA_PRODUCT, "backward-data contraction"))) return st;
   if (big_side(p) && p->method != OAA_METHOD_OVERLAP_SAVE)
     return big_inverse(cx, OAA_STAGE_BWD_DATA_INVERSE, "inverse transform + block crop", region(cx, OAA_REGION_PRODUCT),
-                       1, 0, dx, p->B, p->C, p->N, p->b, 0, p->T, p->b, 0, false);
+                       1, 0, dx, p->B, p->C, p->N, p->b, 0, p->T, p->b, 0, 0);
   if (big_side(p) && (oaa::big_overlap_supported(p->L, p->T) || p->L >= OAA_TWO_STEP_MIN_L ||
                       oaa::big_overlap_few(p->L, long(p->B) * p->C, p->T)))
     return big_inverse(cx, OAA_STAGE_BWD_DATA_INVERSE, "inverse transform + overlap-add",
-                       region(cx, OAA_REGION_PRODUCT), 1, 0, dx, p->B, p->C, p->N, p->b, 0, p->T, p->L, p->n - 1, true);
+                       region(cx, OAA_REGION_PRODUCT), 1, 0, dx, p->B, p->C, p->N, p->b, 0, p->T, p->L, p->n - 1, 1);
   if (p->method == OAA_METHOD_OVERLAP_SAVE) {
     // overlap-add of the gradient blocks' results into dx. The contraction
     // used conj(W): each inverse is a circular correlation with support
     // [-(n-1), h), i.e. the block's convolution with the flipped kernel
     // circularly shifted up and left by n-1; the kernel shifts it back.
+    if (const int how = oaa::wide_overlap(p->L, long(p->B) * p->C, p->T, p->b))
+      return big_inverse(cx, OAA_STAGE_BWD_DATA_INVERSE, "inverse transform + overlap-add",
+                         region(cx, OAA_REGION_PRODUCT), 1, 0, dx, p->B, p->C, p->N, p->b, 0, p->T, p->L, p->n - 1,
+                         how);
     oaa::FoldCropParams o{};
     o.src = region(cx, OAA_REGION_PRODUCT);
     o.dst = dx;
@@ -693,7 +749,7 @@ oaa_status_t backward_filter_pass(const Ctx& cx, const float* x, const float* g,
       return st;
     return big_inverse(cx, OAA_STAGE_BWD_FILTER_INVERSE, "inverse transform of weight gradient",
                        region(cx, OAA_REGION_PRODUCT), p->fsplit, (size_t)p->F * p->C * p->K, dw, p->K, p->C, p->n,
-                       p->n, 0, 1, p->n, 0, false);
+                       p->n, 0, 1, p->n, 0, 0);
   }
   if (g && (st = run_grad_fft(cx, g))) return st;
   // dWhat^T[f] (C x K) = conj(Xhat[f]) (C x BP) * Ghat[f]^T (BP x K), split over BP
@@ -717,7 +773,7 @@ oaa_status_t backward_filter_pass(const Ctx& cx, const float* x, const float* g,
   if (big_side(p))
     return big_inverse(cx, OAA_STAGE_BWD_FILTER_INVERSE, "inverse transform of weight gradient",
                        region(cx, OAA_REGION_PRODUCT), p->split, (size_t)p->F * p->C * p->K, dw, p->K, p->C, p->n,
-                       p->n, 0, 1, p->n, (p->L - origin) & (p->L - 1), false);
+                       p->n, 0, 1, p->n, (p->L - origin) & (p->L - 1), 0);
   oaa::CropParams c{};
   c.src = region(cx, OAA_REGION_PRODUCT);
   c.nsplit = p->split;

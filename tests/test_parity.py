@@ -708,6 +708,37 @@ def test_transforms_spread_over_lanes(gpu_lib, shape):
                 method=binding.METHOD_OVERLAP_SAVE if method == "oas" else binding.METHOD_OVERLAP_ADD)
 
 
+@pytest.mark.parametrize("shape", [
+    (1, 3, 4, 32, 5, 16, 5, "oaa"),       # side 16: kernel and input spectra in one launch, two tiles per wave
+    (2, 10, 13, 75, 2, 16, 15, "oaa"),    # the same with 600 tiles in fours
+    (1, 1, 9, 93, 15, 32, 15, "oaa"),     # side 32: blocks of less than half a tile, more of them than one by one takes
+    (3, 1, 20, 41, 9, 32, 24, "oaa"),     # output blocks one by one
+    (5, 19, 27, 61, 9, 32, 24, "oaa"),    # output planes of nine tiles
+    (3, 3, 20, 43, 10, 32, 0, "oas"),     # overlap-save windows; the error propagation one block more per side
+    (16, 24, 3, 43, 10, 32, 0, "oas"),    # its planes
+    (2, 40, 30, 57, 9, 32, 24, "oaa"),    # 1200 kernel tiles: a sequence per lane again
+    (10, 41, 5, 57, 9, 32, 24, "oaa"),    # 3690 input tiles in sixteens, ragged
+    (22, 2, 60, 110, 9, 32, 24, "oaa"),   # 33000 gradient windows, five per side
+], ids=lambda s: "x".join(map(str, s)))
+def test_small_sides_spread_over_lanes(gpu_lib, shape):
+    """Sides 16 and 32 on the kernels that spread a transform over lanes, over
+    their tiles per workgroup and output modes, against the oracle; spectra are
+    the same bit for bit whether kernels and input go through one launch or,
+    with per-stage timing or a cached spectrum, through two."""
+    B, C, K, N, n, L, b, method = shape
+    x, w, g = make_inputs(Layer("t", B, C, K, N, n), seed=47 + sum(shape[:7]))
+    m = binding.METHOD_OVERLAP_SAVE if method == "oas" else binding.METHOD_OVERLAP_ADD
+    check_whole(x, w, g, tiling=(L, b), method=m)
+    plan = binding.Plan(B, C, K, N, n, device=DEV, tiling=(L, b), method=m)
+    xd, wd = to_dev(x), to_dev(w)
+    y = plan.forward(xd, wd)
+    assert torch.equal(y, plan.forward(xd, None))
+    plan.set_timing(True)
+    assert torch.equal(y, plan.forward(xd, wd))
+    times = plan.stage_times()
+    assert times["w_spectrum"][1] == 1 and times["x_spectrum"][1] == 1
+
+
 def test_stage_spectra_match_oracle_steps(gpu_lib):
     """Workspace spectra (kernel, input blocks, gradient windows, products)
     against the OaA steps of the oracle, in the layouts oaa.h documents."""
