@@ -100,14 +100,19 @@ def test_matrix_core_tile_shapes(gpu_lib, shape):
 
 
 @pytest.mark.parametrize("shape", [
-    (2, 5, 9, 20, 3, 16, 14),       # one slice or less of every reduction: 32 x 32 tiles
-    (5, 19, 27, 61, 9, 32, 24),     # odd sizes, ragged reductions: 32 x 64, 32 x 32
-    (3, 6, 40, 60, 5, 16, 12),      # few rows: 64 x 32, 16 x 64
-    (8, 5, 7, 60, 3, 16, 14),       # 16 x 128, split reduction
-    (30, 7, 150, 20, 3, 8, 6),      # 96 x 96, 16 x 64, 16 x 128
+    (2, 5, 9, 20, 3, 16, 14),       # one slice or less of every reduction: 16 x 64 tiles
+    (5, 19, 27, 61, 9, 32, 24),     # odd sizes, ragged reductions: 32 x 32
+    (3, 6, 40, 60, 5, 16, 12),      # few rows; split reduction
+    (8, 5, 7, 60, 3, 16, 14),       # every extent below a tile's
+    (30, 7, 150, 20, 3, 8, 6),      # 64 x 96, 16 x 64
     (30, 150, 7, 20, 3, 8, 6),      # 64 x 16
-    (8, 100, 200, 30, 3, 16, 14),   # 64 x 96, 128 x 64
-    (40, 96, 96, 30, 3, 16, 14),    # 96 x 96 in all three passes
+    (19, 78, 106, 15, 3, 8, 6),     # 16 x 128
+    (16, 64, 64, 30, 3, 16, 14),    # 64 x 32, 32 x 64
+    (8, 100, 200, 30, 3, 16, 14),   # 96 x 96, 64 x 32, 128 x 64
+    (40, 96, 96, 30, 3, 16, 14),    # 96 x 64, 96 x 96
+    (8, 256, 96, 60, 5, 32, 28),    # 96 x 96, 64 x 96, 128 x 96
+    (10, 96, 256, 60, 9, 32, 24),   # 96 x 128
+    (1, 97, 197, 49, 16, 64, 49),   # one column; 128 x 128
 ], ids=lambda s: "x".join(map(str, s)))
 def test_matrix_core_split(gpu_lib, shape):
     """The contraction on three bf16 pieces per value, over its tile shapes,
