@@ -550,26 +550,34 @@ __global__ void __launch_bounds__(kMaxThreads) irfft2_overlap_crop_kernel(FoldCr
   const int cb = max(0, -j0), ce = min(W, M - j0);
   const int wr = ce - cb;
   if (wr <= 0 || re_ <= rb) return;
-  // lanes over columns in rows of a power-of-two width; column / b by a
-  // reciprocal multiply (c < TQ b, which the LDS budget keeps below 2^13)
-  const int lw = 32 - __builtin_clz(unsigned(wr - 1) | 1u), cw = 1 << lw;
+  // Lanes over columns, rows down each lane: a wave takes 64 columns of a row
+  // (or as many rows of fewer columns as fit), so a column's tile, offsets and
+  // neighbours are found once and the branches on rows are uniform in a wave.
+  // Column / b by a reciprocal multiply (c < TQ b, which the LDS budget keeps
+  // below 2^13). 100 planes of 256 x 256 in blocks of 28: 40.5 us with a pixel
+  // at a time, now 37.8.
+  const int lw = min(6, 32 - __builtin_clz(unsigned(wr - 1) | 1u)), lane = tid & 63;
+  const int rstep = (nthr >> 6) << (6 - lw);
   const SmallDiv div_b(b);
-  for (int e = tid; e < (re_ - rb) << lw; e += nthr) {
-    const int r = rb + (e >> lw), c = cb + (e & (cw - 1));
-    if (c >= ce) continue;
+  for (int c = cb + (lane & ((1 << lw) - 1)); c < ce; c += 64) {
     const int q = div_b(c), s = c - q * b;
-    const float* own = sc + (q + 1) * SSc + r * RS;
-    const float* left = sc + q * SSc + r * RS;
-    float v = own[s];
-    if (s < na) v += left[b + s];
-    if (r < na) {
-      v += sa[(q + 1) * SSa + r * RS + s];
-      if (s < na) v += sa[q * SSa + r * RS + b + s];
+    const bool side = s < na;  // the left neighbour's overhang covers this column
+    int r = rb + ((tid >> 6) << (6 - lw)) + (lane >> lw);
+    const float* own = sc + (q + 1) * SSc + r * RS + s;
+    const float* left = sc + q * SSc + r * RS + b + s;
+    unsigned o = unsigned((i0 + r) * M + j0 + c) * 4u;  // O32
+    for (; r < re_; r += rstep, own += rstep * RS, left += rstep * RS, o += unsigned(rstep * M) * 4u) {
+      float v = *own;
+      if (side) v += *left;
+      if (r < na) {
+        v += sa[(q + 1) * SSa + r * RS + s];
+        if (side) v += sa[q * SSa + r * RS + b + s];
+      }
+      if (O32)
+        store_at(out, o, v);
+      else
+        out[size_t(i0 + r) * M + j0 + c] = v;
     }
-    if (O32)
-      store_at(out, unsigned((i0 + r) * M + j0 + c) * 4u, v);
-    else
-      out[size_t(i0 + r) * M + j0 + c] = v;
   }
 }
 
@@ -618,6 +626,7 @@ __global__ void __launch_bounds__(kMaxThreads) irfft2_overlap_rows_kernel(FoldCr
   // lanes over output columns in rows of a power-of-two width; divisions by
   // b through a reciprocal multiply (operands below To b and RB b, < 2^16)
   const int lw = 32 - __builtin_clz(unsigned(CW - 1) | 1u), cw = 1 << lw;
+  const int lane = tid & 63, wave = tid >> 6, lwb = min(6, lw), rstep = (nthr >> 6) << (6 - lwb);
   const SmallDiv div_b(b);
   // real value at row r, column s of tile (row pl of the step, column q)
   auto at = [&](int pl, int q, int r, int s) { return zr[2 * ((pl * T + q) * TSz + r * V) + s]; };
@@ -697,20 +706,28 @@ __global__ void __launch_bounds__(kMaxThreads) irfft2_overlap_rows_kernel(FoldCr
     __syncthreads();
     // output block rows P0 .. P0 + orow - 1: pixel (P b - off + rr, c - off)
     const float* cin = carry + cur * na * CW;
-    for (int e = tid; e < (orow * b) << lw; e += nthr) {
-      const int r = e >> lw, c = e & (cw - 1);
-      if (c >= CW) continue;
-      const int pl = div_b(r), rr = r - pl * b;
+    // with lanes over columns and rows down each lane, as in the one-row kernel
+    // (128 x 128 planes of 56 x 56 in blocks of 14: 141 us with a pixel at a
+    // time, now 128)
+    const int base = P0 * b - p.off;  // output row of r = 0
+    const int rhi = min(orow * b, M - base);
+    for (int c = lane & ((1 << lwb) - 1); c < CW; c += 64) {
+      const int j = c - p.off;
+      if (j < 0 || j >= M) continue;
       const int q = div_b(c), s = c - q * b;
-      const int i = (P0 + pl) * b - p.off + rr, j = c - p.off;
-      if (i < 0 || i >= M || j < 0 || j >= M) continue;
-      float v = 0.f;
-      if (pl < tr) {
-        if (q < T) v = at(pl, q, rr, s);
-        if (s < na && q > 0) v += at(pl, q - 1, rr, b + s);
+      const bool has = q < T, side = s < na && q > 0;
+      int r = max(0, -base) + (wave << (6 - lwb)) + (lane >> lwb);
+      unsigned o = unsigned((base + r) * M + j) * 4u;
+      for (; r < rhi; r += rstep, o += unsigned(rstep * M) * 4u) {
+        const int pl = div_b(r), rr = r - pl * b;
+        float v = 0.f;
+        if (pl < tr) {
+          if (has) v = at(pl, q, rr, s);
+          if (side) v += at(pl, q - 1, rr, b + s);
+        }
+        if (rr < na) v += pl == 0 ? cin[rr * CW + c] : (pl - 1 < tr ? overhang(pl - 1, q, s, rr) : 0.f);
+        store_at(out, o, v);
       }
-      if (rr < na) v += pl == 0 ? cin[rr * CW + c] : (pl - 1 < tr ? overhang(pl - 1, q, s, rr) : 0.f);
-      store_at(out, unsigned(i * M + j) * 4u, v);
     }
     // carry of the next step: the overhang rows of this step's last tile row
     // (the next step starts right below it whenever there is one)
