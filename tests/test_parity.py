@@ -128,6 +128,38 @@ def test_matrix_core_split(gpu_lib, shape):
     assert np.array_equal(y2, y * up) and np.array_equal(dx2, dx / up) and np.array_equal(dw2, dw)
 
 
+@pytest.mark.parametrize("shape", [
+    (2, 3, 5, 20, 3, 8, 6),       # windows of a whole tile (gradient) and smaller (blocks)
+    (3, 5, 6, 58, 3, 16, 14),     # planes past the last whole block
+    (2, 5, 5, 40, 5, 16, 8),      # windows smaller than the tile, more than half of it
+    (2, 6, 5, 60, 3, 16, 4),      # at most half of it
+    (1, 9, 40, 90, 5, 32, 28),
+    (2, 40, 40, 61, 5, 32, 28),   # odd side: the 4-byte loads in both
+    (2, 5, 6, 30, 4, 16, 12),     # odd framing of the gradient
+], ids=lambda s: "x".join(map(str, s)))
+def test_window_loads_by_alignment(gpu_lib, shape):
+    """8-byte window loads (even sizes, tensors aligned to 8 bytes) against the
+    4-byte loads of the same call on tensors that start at an odd element: the
+    same values enter the same transforms, so the results are equal bit by bit."""
+    B, C, K, N, n, L, b = shape
+    x, w, g = make_inputs(Layer("t", B, C, K, N, n), seed=43 + sum(shape))
+    check_whole(x, w, g, tiling=(L, b))
+    plan = binding.Plan(B, C, K, N, n, device=DEV, tiling=(L, b))
+    wd = to_dev(w)
+
+    def shifted(a):
+        t = torch.empty(a.size + 1, device=DEV)[1:].view(a.shape)
+        t.copy_(to_dev(a))
+        return t
+
+    def passes(xd, gd):
+        out = plan.forward(xd, wd), plan.backward_data(gd, wd), plan.backward_filter(xd, gd)
+        return [o.clone() for o in out]
+
+    even, odd = passes(to_dev(x), to_dev(g)), passes(shifted(x), shifted(g))
+    assert all(torch.equal(a, c) for a, c in zip(even, odd))
+
+
 NARROW = [  # C <= 4: odd and even tile counts, K off multiples of 16, K > 64, K > 256, split reduction
     (1, 1, 1, 9, 3),
     (2, 2, 17, 13, 4),
