@@ -100,7 +100,8 @@ def source_digest(fname):
     return h.hexdigest()[:16]
 
 
-KERNEL_FILES = (("big_", "k_big_fft.hip"), ("overlap_gather", "k_big_fft.hip"), ("fused_", "k_fused.hip"),
+KERNEL_FILES = (("wide_", "k_wide_fft.hip"), ("big_", "k_big_fft.hip"),
+                ("overlap_gather", "k_big_fft.hip"), ("fused_", "k_fused.hip"),
                 ("cgemm_", "k_cgemm.hip"), ("narrow_", "k_narrow.hip"), ("irfft2_fold", "k_fold_fft.hip"),
                 ("irfft2_overlap", "k_fold_fft.hip"), ("tile_rfft2", "k_tile_fft.hip"),
                 ("window_", "k_tile_fft.hip"), ("irfft2_crop", "k_tile_fft.hip"))
