@@ -142,7 +142,7 @@ def measured_traffic(workload, geo, stage):
 
 
 def measured_mfma(workload, geo, stage):
-    """Matrix-core counters of a contraction stage (busy fraction and fp32
+    """Matrix-core counters of a contraction stage (busy fraction and
     MFMA flops per launch) from committed rocprofv3 runs, or None."""
     rec = _profile_record("mfma.json", workload, geo, stage)
     if rec is None:
@@ -182,7 +182,7 @@ def cpu_baseline(ly, x, w, g, budget_s=20.0):
 STAGE_ORDER = ["w_spectrum", "x_spectrum", "fwd_product", "fwd_inverse", "g_spectrum", "bwd_data_product",
                "bwd_data_inverse", "bwd_filter_product", "bwd_filter_inverse"]
 LIB_KERNELS = ("tile_rfft2_kernel", "window_rfft2_kernel", "window_rows_rfft2_kernel", "irfft2_", "cgemm_", "narrow_",
-               "big_rfft2", "big_irfft2", "overlap_gather", "fused_")
+               "big_rfft2", "big_irfft2", "wide_rfft2", "wide_irfft2", "overlap_gather", "fused_")
 
 
 def stage_sequence(geo):
@@ -290,8 +290,8 @@ def summarize_counters(layer, run_dir, steps=2, method="oaa"):
     `bench.py --layer <layer> --method <method> --steps 2 --warmup 1
     --no-cpu-baseline` (mean over the last `steps` steps). For the
     contractions, the matrix-core figures (MfmaUtil: busy cycles of the
-    MFMA units over active cycles of all SIMDs; MfmaFlopsF32 and the XF32 /
-    BF16 MFMA op counts) are recorded in profiles/mfma.json."""
+    MFMA units over active cycles of all SIMDs; MfmaFlopsF32 and the XF32 and
+    BF16 MFMA flops) are recorded in profiles/mfma.json."""
     import csv
     import glob
     from paper_1601_06815_amd import binding
