@@ -747,10 +747,10 @@ __global__ void __launch_bounds__(kMaxThreads, fft_waves<L>(OAA_WAVES_CROP)) irf
   __syncthreads();
   // Lanes over the columns (q, s) of the tiles in order: neighbouring tiles of
   // a block row are neighbours in the output row. A lane takes up to four
-  // rows, G apart (fewer where columns alone leave lanes idle), so that the divisions, the tile's descriptor and the
-  // address are taken once per column: a pixel at a time, this loop was two
-  // thirds of the kernel's vector instructions (128 x 128 planes of 4 x 4
-  // tiles of side 16: 172 us, now 156).
+  // rows, G apart (fewer where columns alone leave lanes idle), so that the
+  // divisions, the tile's descriptor and the address are taken once per column:
+  // a pixel at a time, this loop was two thirds of the kernel's vector
+  // instructions (128 x 128 planes of 4 x 4 tiles of side 16: 172 us, now 156).
   // (n * nq * n < 2^16: launcher)
   const int W = nq * n, G = max((n + 3) >> 2, min(n, nthr / W));
   const SmallDiv div_n(n), div_w(W);

@@ -1,9 +1,11 @@
-// Transforms of side L = 128, and of side 64 in launches of few tiles
-// (arXiv:1601.06815, Section 2: block division, zero padding, the per-block
-// transforms and the overlap-add; Section 3.3 for the transform sides of large
-// kernels), with each L-point transform spread over lanes.
+// Transforms of side L = 128, and of sides 16 to 64 in launches of few tiles
+// or in the shapes that the other kernels serve less well (wide_takes,
+// wide_overlap, wide_pair_fits) (arXiv:1601.06815, Section 2: block division,
+// zero padding, the per-block transforms and the overlap-add; Section 3.3 for
+// the transform sides of large kernels), with each L-point transform spread
+// over lanes.
 //
-// L = N1 x 8. With n = 8 n1 + n2 and k = k1 + N1 k2,
+// L = N1 x 8 (4 x 4 at L = 16). With n = 8 n1 + n2 and k = k1 + N1 k2,
 //   X[k1 + N1 k2] = sum_n2 w8^(n2 k2) ( wL^(n2 k1) sum_n1 wN1^(n1 k1) x[8 n1 + n2] ),
 // so a transform takes two passes over LDS: N1-point transforms over the
 // elements of one n2 with a twiddle, then 8-point transforms over n2. Both
