@@ -38,9 +38,25 @@ constexpr int kThreads = 256;
 constexpr int kKB = 256;       // kernel spectra staged per LDS block
 constexpr int kIter = 4;       // groups of VEC tiles per lane (forward, backward_data)
 constexpr int kKG = 16;        // kernels per wave (backward_filter)
-// B P below which the few-tile variants of forward and backward_data run: the
-// others give a workgroup 2048 tiles (or 1024 where rows are not even).
+// B P below which the few-tile variants of forward and backward_data may run:
+// the others give a workgroup 2048 tiles (or 1024 where rows are not even).
 constexpr int kFewTiles = 1024;
+// The few-tile forward reads 2 C operands for each VEC results, the other one
+// each input spectrum once for all kernels, in one workgroup per bin. So it
+// runs up to kFewForwardAlways tiles, and while C (B P / VEC) F, the input
+// units of all bins, stays below kFewForward. Measured, in us with the stage's
+// events, the other first, as (C, K, B P, L): at 50 000 units (2,50,384,16)
+// 13.6 / 10.5, 111 000 (4,26,108,32) 13.5 / 9.6, 116 000 (3,80,297,16) 23.6 /
+// 20.2, 148 000 (4,54,144,32) 17.4 / 17.2, 166 000 (4,67,81,32) 17.1 / 19.8,
+// 198 000 (3,47,507,16) 14.9 / 16.7, 319 000 (3,60,207,32) 16.4 / 28.5, 721 000
+// (2,76,352,64) 71 / 89.
+constexpr int kFewForwardAlways = 64;
+constexpr long kFewForward = 160000;
+// C B P below which the few-tile backward_data runs, measured likewise:
+// (2,50,384,16) 24.1 / 11.1, (1,93,832,32) 96 / 87, (4,21,288,32) 17.9 / 16.2,
+// (4,76,369,32) 39 / 46, (4,18,432,32) 16.4 / 17.5, (4,8,928,32) 12.2 / 15.6;
+// past the line it won only at L = 16, (3,47,507,16) 22.7 / 15.5.
+constexpr long kFewBwdData = 1440;
 constexpr int kFewPerLane = 8;     // results per lane of the forward variant (many results)
 constexpr int kFewThreads = 1024;  // most lanes of the backward_data variant
 
@@ -336,17 +352,23 @@ __global__ void __launch_bounds__(kFewThreads) narrow_bwd_data_few_kernel(GemmPa
 #pragma unroll
   for (int c = 0; c < CN; ++c) red[c][t] = acc[c];
   __syncthreads();
+  // halves added pairwise: 625 kernels on one tile of 16 points leave 512 sums,
+  // which one lane added in turn for most of the kernel's 13.4 us
+  for (int h = nk >> 1; h > 0; h >>= 1) {
+    if (lane >> nb_log2 < h) {
+#pragma unroll
+      for (int c = 0; c < CN; ++c) {
+        const float2 v = red[c][t + (h << nb_log2)];
+        acc[c].x += v.x;
+        acc[c].y += v.y;
+        red[c][t] = acc[c];
+      }
+    }
+    __syncthreads();
+  }
   if (live && lane <= mask && j < BP) {
 #pragma unroll
-    for (int c = 0; c < CN; ++c) {
-      float2 sum = make_float2(0.f, 0.f);
-      for (int q = 0; q < nk; ++q) {
-        const float2 v = red[c][t + (q << nb_log2)];
-        sum.x += v.x;
-        sum.y += v.y;
-      }
-      O[c * p.ldc + j] = sum;
-    }
+    for (int c = 0; c < CN; ++c) O[c * p.ldc + j] = acc[c];
   }
 }
 
@@ -445,10 +467,12 @@ bool pairs_ok(long ld, long chunk, int nsplit) { return ld % 2 == 0 && (nsplit =
 template <int CN>
 hipError_t launch_narrow_c(const GemmParams& p, hipStream_t s) {
   const bool few = p.N >= 1 && p.N < kFewTiles && p.nsplit == 1;
-  if (few && p.a_trans && !p.a_conj && !p.b_trans && !p.b_conj && p.ldc == p.N &&
-      (unsigned long long)p.M * p.N < (1ull << 26))
-    return p.N % 2 == 0 ? launch_fwd_few<CN, 2>(p, s) : launch_fwd_few<CN, 1>(p, s);
-  if (few && !p.a_trans && p.a_conj && !p.b_trans && !p.b_conj) return launch_bwd_data_few<CN>(p, s);
+  const int vec = p.N % 2 == 0 ? 2 : 1;
+  if (few && (p.N <= kFewForwardAlways || long(CN) * (p.N / vec) * p.F < kFewForward) && p.a_trans && !p.a_conj &&
+      !p.b_trans && !p.b_conj && p.ldc == p.N && (unsigned long long)p.M * p.N < (1ull << 26))
+    return vec == 2 ? launch_fwd_few<CN, 2>(p, s) : launch_fwd_few<CN, 1>(p, s);
+  if (few && long(CN) * p.N < kFewBwdData && !p.a_trans && p.a_conj && !p.b_trans && !p.b_conj)
+    return launch_bwd_data_few<CN>(p, s);
   if (p.Kr >= 1 && p.Kr <= kFewTilesFilter && p.nsplit == 1 && !p.a_trans && p.a_conj && p.b_trans && !p.b_conj) {
     hipLaunchKernelGGL(narrow_bwd_filter_few_kernel<CN>, dim3(unsigned((p.N + kThreads - 1) / kThreads), unsigned(p.F)),
                        dim3(kThreads), 0, s, p);

@@ -177,6 +177,9 @@ NARROW = [  # C <= 4: odd and even tile counts, K off multiples of 16, K > 64, K
     (1, 3, 500, 48, 5, 16, 12),    # 16 tiles, many kernels: pairs of results, ranges of a bin
     (3, 4, 9, 100, 5, 16, 12),     # 243 tiles
     (2, 1, 40, 130, 5, 16, 8),     # 578 tiles: ranges of tiles in the error propagation
+    (1, 1, 625, 8, 5, 16, 8),      # one tile: 512 partial sums added pairwise
+    (1, 3, 7, 168, 5, 16, 8),      # 441 tiles of three channels: few-tile error propagation only
+    (2, 4, 5, 120, 5, 16, 8),      # 450 tiles of four channels: few-tile forward only
     (4, 1, 3, 130, 3, 8, 6),       # 1936 tiles: past the few-tile kernels
 ], ids=lambda s: "x".join(map(str, s)))
 def test_few_tiles_per_bin(gpu_lib, shape):
