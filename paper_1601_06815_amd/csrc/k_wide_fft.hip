@@ -217,8 +217,9 @@ __global__ void __launch_bounds__(kWideMaxThreads) wide_rfft2_kernel(BigFwdParam
       const float2 a = at(v), c = at((L - v) % L);
       const int t = t0 + q;
       float2* out = p.dst + size_t(ch) * p.cs + size_t(t / p.run) * p.rs + size_t(t % p.run);
-      out[size_t(v) * bs] = make_float2(0.5f * (a.x + c.x), 0.5f * (a.y - c.y));
-      out[(size_t(H2) * V + v) * bs] = make_float2(0.5f * (a.y + c.y), 0.5f * (c.x - a.x));
+      // halved before they are added: the sums of bins past 1.7e38 would overflow
+      out[size_t(v) * bs] = make_float2(0.5f * a.x + 0.5f * c.x, 0.5f * a.y - 0.5f * c.y);
+      out[(size_t(H2) * V + v) * bs] = make_float2(0.5f * a.y + 0.5f * c.y, 0.5f * c.x - 0.5f * a.x);
     }
     __syncthreads();
   }
@@ -385,9 +386,9 @@ __global__ void __launch_bounds__(kWideMaxThreads) wide_irfft2_kernel(BigInvPara
             if (!has(q) || a >= KR || cc >= KR) continue;
             int second;
             const int rb = row_base(q, a, second);
-            acc += at(rb, second, cc);
+            acc = __builtin_fmaf(scale, at(rb, second, cc), acc);
           }
-          out[size_t(i0 + r) * H + j0 + c] = acc * scale;
+          out[size_t(i0 + r) * H + j0 + c] = acc;
         }
       }
     } else if (MODE == 1) {
@@ -406,13 +407,13 @@ __global__ void __launch_bounds__(kWideMaxThreads) wide_irfft2_kernel(BigInvPara
             if (!on) return;
             int second;
             const int rb = row_base(Pt * T + Qt, ra, second);
-            acc += at(rb, second, ca);
+            acc = __builtin_fmaf(scale, at(rb, second, ca), acc);
           };
           add(r0 && c0, P1 - 1, Q1 - 1, ra1 + b, ca1 + b);
           add(r0 && c1, P1 - 1, Q1, ra1 + b, ca1);
           add(r1 && c0, P1, Q1 - 1, ra1, ca1 + b);
           add(r1 && c1, P1, Q1, ra1, ca1);
-          out[size_t(i) * H + jx] = acc * scale;
+          out[size_t(i) * H + jx] = acc;
         }
       }
     } else {

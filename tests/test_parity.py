@@ -128,6 +128,23 @@ def test_matrix_core_split(gpu_lib, shape):
     assert np.array_equal(y2, y * up) and np.array_equal(dx2, dx / up) and np.array_equal(dw2, dw)
 
 
+@pytest.mark.parametrize("L, b, n, which", [(16, 14, 3, "x"), (16, 14, 3, "w"), (32, 28, 5, "x"), (32, 28, 5, "w"),
+                                            (32, 28, 5, "g")])
+def test_transforms_near_the_top(gpu_lib, L, b, n, which):
+    """A bin of 3e38 in the spectra that the lane-spread kernels make of few
+    tiles of sides 16 and 32 (a constant block, kernel or gradient, whose bin
+    (0, 0) is its sum): nothing on the way to it or from it overflows."""
+    N = 2 * b
+    x, w, g = make_inputs(Layer("t", 1, 1, 2, N, n), seed=61 + L)
+    if which == "x":
+        x[...], w, g = 3e38 / b**2, w * np.float32(2.0**-40), g * np.float32(2.0**-40)
+    elif which == "w":
+        x, w[...], g = x * np.float32(2.0**-40), 3e38 / n**2, g * np.float32(2.0**-40)
+    else:  # b rows and columns of each gradient window are inside the plane
+        x, w, g[...] = x * np.float32(2.0**-40), w * np.float32(2.0**-40), 3e38 / b**2
+    check_whole(x, w, g, tiling=(L, b))
+
+
 @pytest.mark.parametrize("shape", [
     (2, 3, 5, 20, 3, 8, 6),       # windows of a whole tile (gradient) and smaller (blocks)
     (3, 5, 6, 58, 3, 16, 14),     # planes past the last whole block
