@@ -126,7 +126,10 @@ typedef enum {
 typedef enum {
   OAA_CONTRACTION_AUTO = 0,  /* library's choice by shape                        */
   OAA_CONTRACTION_VALU = 1,  /* LDS-tiled FMA on the vector ALUs                 */
-  OAA_CONTRACTION_MFMA = 2,  /* matrix cores, fp32 values as three bf16 pieces   */
+  OAA_CONTRACTION_MFMA = 2,  /* matrix cores, fp32 values as three bf16 pieces
+                                (results of values that those do not hold, below
+                                2^-110 or above 3.396e38, in fp32 on the vector
+                                ALUs: several times slower)                     */
   OAA_CONTRACTION_NARROW = 3, /* streaming, for C <= 4 input channels only      */
   OAA_CONTRACTION_FUSED = 4   /* the contraction inside the transform kernels, so
                                  that the product spectra (forward) and the

@@ -19,7 +19,9 @@
 //  * bf16 matrix cores (v_mfma_f32_16x16x32_bf16) on operands split exactly
 //    into three bf16 pieces each, with fp32 accumulation: 16 x 64 to 128 x 128
 //    complex tiles per workgroup, persistent workgroups walking the tiles in
-//    XCD-local rounds, operands read through buffer resources.
+//    XCD-local rounds, operands read through buffer resources. Results of
+//    values that three pieces do not hold (below 2^-110, above 3.396e38) are
+//    taken again in fp32 multiply-adds.
 #include <algorithm>
 #include <atomic>
 #include <cmath>
@@ -177,9 +179,13 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // A complex value as three complex bf16 pieces, each packed (re low, im
-// high): x = p0 + p1 + p2 exactly, since each rounding to nearest leaves a
-// remainder of at most 16 and then 8 significant bits of the 24.
-__device__ __forceinline__ void split3(float2 x, unsigned& p0, unsigned& p1, unsigned& p2) {
+// high): x = p0 + p1 + p2 exactly for components of 2^-110 to 3.396e38, since
+// each rounding to nearest leaves a remainder of at most 16 and then 8
+// significant bits of the 24, none below bf16's smallest number, 2^-133. Of a
+// smaller component the last remainder may have bits below that; they are in
+// its low 16 bits, which are or-ed to `lost`. A larger one rounds to infinity,
+// and the remainder, infinity minus infinity in the end, to NaN.
+__device__ __forceinline__ void split3(float2 x, unsigned& p0, unsigned& p1, unsigned& p2, unsigned& lost) {
   auto pack = [](float a, float b) {
     return __builtin_bit_cast(unsigned, __builtin_convertvector(floatx2{a, b}, bf16x2));
   };
@@ -188,7 +194,9 @@ __device__ __forceinline__ void split3(float2 x, unsigned& p0, unsigned& p1, uns
   p0 = pack(x.x, x.y);
   const float r1 = x.x - lo(p0), i1 = x.y - hi(p0);
   p1 = pack(r1, i1);
-  p2 = pack(r1 - lo(p1), i1 - hi(p1));
+  const float r2 = r1 - lo(p1), i2 = i1 - hi(p1);
+  p2 = pack(r2, i2);
+  lost |= __builtin_bit_cast(unsigned, r2) | __builtin_bit_cast(unsigned, i2);
 }
 
 // LDS image of an operand's ROWS x kKC slice, one per piece: rows of four
@@ -254,20 +262,24 @@ struct Operand {
     }
   }
 
+  // A quad that its pieces lose bits of gets a piece that is NaN, as one with a
+  // component too large has already.
   __device__ __forceinline__ void store(uintx4* lds) const {
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int t = task(i);
       if (!WHOLE && t >= TASKS) continue;
       uintx4 q0, q1, q2;
+      unsigned lost = 0;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         unsigned a, b, c;
-        split3(v[i][j], a, b, c);
+        split3(v[i][j], a, b, c, lost);
         q0[j] = a;
         q1[j] = b;
         q2[j] = c;
       }
+      if (static_cast<unsigned short>(lost) != 0) q2[0] = ~0u;
       uintx4* at = lds + quad_at(row_of(t), quad_of(t));
       at[0] = q0;
       at[TASKS] = q1;
@@ -275,6 +287,8 @@ struct Operand {
     }
   }
 };
+
+constexpr float kMaxFloat = 0x1.fffffep127f;
 
 __device__ __forceinline__ floatx4 mfma(bf16x8 a, bf16x8 b, floatx4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
@@ -317,7 +331,8 @@ constexpr size_t mfma_lds_bytes(int TM, int TN) { return size_t(TM + TN) * 4 * 1
 // imaginary part with (bi, br) (conjugated a: (br, bi) and (bi, -br)), both
 // made from the packed (br, bi) in registers. Of the nine products of the
 // pieces, the six of order up to 2^-16 are taken; the three left out are
-// below 2^-24 of the product, under fp32's own rounding of it. Each slice's
+// below 2^-24 of the product, under fp32's own rounding of it (the matrix cores
+// take and keep subnormal bf16 and fp32 values). Each slice's
 // products are summed in accumulators of their own, the smallest first, and
 // added to the tile's once: adding all six straight to the tile's left a
 // reduction over 256 tiles at 4.9e-7 relative error against 64 bits, where
@@ -397,6 +412,49 @@ __global__ void __launch_bounds__(64 * WM * WN, 2) cgemm_mfma_kernel(GemmParams 
       }
   };
   zero();
+
+  // The wave's results of a tile in fp32 multiply-adds, with operands straight
+  // from memory: where results are infinite or NaN, which they are where the
+  // pieces do not hold an operand (see split3). All results of the middle layer
+  // (128 channels, 56 x 56) so: 1.3 ms for the forward product, 0.25 without.
+  auto again = [&](const MfmaTile& t) {
+    zero();
+    const float2* A = p.A + size_t(t.f) * p.a_fstride;
+    const float2* B = p.B + size_t(t.f) * p.b_fstride;
+    unsigned oa[MB][4], ob[NB];
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const unsigned m = unsigned(min(t.m0 + wm + 16 * i + 4 * lk + r, p.M - 1));
+        oa[i][r] = AT ? m : m * unsigned(p.lda);
+      }
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const unsigned n = unsigned(min(t.n0 + wn + 16 * j + lr, p.N - 1));
+      ob[j] = BT ? n * unsigned(p.ldb) : n;
+    }
+#pragma unroll 1
+    for (int k = t.kb; k < t.ke; ++k) {
+      const unsigned ka = AT ? unsigned(k) * unsigned(p.lda) : unsigned(k);
+      const unsigned kb = BT ? unsigned(k) : unsigned(k) * unsigned(p.ldb);
+      float2 b[NB];
+#pragma unroll
+      for (int j = 0; j < NB; ++j) b[j] = B[kb + ob[j]];
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          float2 a = A[ka + oa[i][r]];
+          if (AC) a.y = -a.y;
+#pragma unroll
+          for (int j = 0; j < NB; ++j) {
+            cr[i][j][r] = __builtin_fmaf(-a.y, b[j].y, __builtin_fmaf(a.x, b[j].x, cr[i][j][r]));
+            ci[i][j][r] = __builtin_fmaf(a.y, b[j].x, __builtin_fmaf(a.x, b[j].y, ci[i][j][r]));
+          }
+        }
+    }
+  };
 
   int buf = 0;
   for (;;) {
@@ -498,6 +556,19 @@ __global__ void __launch_bounds__(64 * WM * WN, 2) cgemm_mfma_kernel(GemmParams 
     }
     __builtin_amdgcn_s_setprio(0);
     if (ck + kKC >= cur.ke) {
+      // the largest result, or NaN if there is one (maximum, not max)
+      float most[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            most[r] = __builtin_elementwise_maximum(
+                most[r], __builtin_elementwise_maximum(__builtin_fabsf(cr[i][j][r]), __builtin_fabsf(ci[i][j][r])));
+      const float all = __builtin_elementwise_maximum(__builtin_elementwise_maximum(most[0], most[1]),
+                                                      __builtin_elementwise_maximum(most[2], most[3]));
+      if (__builtin_expect(__any(!(all <= kMaxFloat)), 0)) again(cur);
       // 16 x 16 result block: lane holds rows 4*(lane/16) + r, r < 4, of column
       // lane % 16; each bin's matrix is under 2^28 elements (32-bit offsets)
       float2* Cm = p.C + size_t(cur.f) * p.c_fstride + size_t(cur.split) * p.c_sstride;

@@ -116,9 +116,9 @@ def test_matrix_core_tile_shapes(gpu_lib, shape):
 ], ids=lambda s: "x".join(map(str, s)))
 def test_matrix_core_split(gpu_lib, shape):
     """The contraction on three bf16 pieces per value, over its tile shapes,
-    against the oracle; and scaling an input by a power of two scales the
-    results exactly, as it does every fp32 step of the path (the pieces have
-    fp32's exponent range)."""
+    against the oracle; and scaling an input by a power of two, to magnitudes
+    whose pieces are exact, scales the results exactly, as it does every fp32
+    step of the path."""
     B, C, K, N, n, L, b = shape
     x, w, g = make_inputs(Layer("t", B, C, K, N, n), seed=37 + sum(shape))
     check_whole(x, w, g, tiling=(L, b))
@@ -143,6 +143,85 @@ def test_transforms_near_the_top(gpu_lib, L, b, n, which):
     else:  # b rows and columns of each gradient window are inside the plane
         x, w, g[...] = x * np.float32(2.0**-40), w * np.float32(2.0**-40), 3e38 / b**2
     check_whole(x, w, g, tiling=(L, b))
+
+
+RANGE = [  # (B, C, K, N, n, L, b): small tiles, a split reduction, 16 x 128, 128 x 64, 128 x 128 tiles
+    (2, 5, 9, 20, 3, 16, 14),
+    (3, 6, 40, 60, 5, 16, 12),
+    (19, 78, 106, 15, 3, 8, 6),
+    (8, 100, 200, 30, 3, 16, 14),
+    (1, 97, 197, 49, 16, 64, 49),
+]
+
+
+def check_groups(got, ref, axis):
+    """relerr of the even and of the odd slices along an axis, each by its own largest value."""
+    for part in (slice(0, None, 2), slice(1, None, 2)):
+        at = (slice(None),) * axis + (part,)
+        e = relerr(got[at], ref[at])
+        assert e <= TOL, (axis, part, e)
+
+
+@pytest.mark.parametrize("which", ["x", "w", "g", "channels", "images"])
+@pytest.mark.parametrize("shape", RANGE, ids=lambda s: "x".join(map(str, s)))
+def test_contraction_of_tiny_values(gpu_lib, shape, which):
+    """Operands near the bottom of fp32's normal numbers, where a value's
+    lowest bits are below bf16's smallest number, keep fp32's precision:
+    everywhere, or in every other channel or image, with the other operand as
+    large in those, so that both kinds weigh alike in the sums over them."""
+    B, C, K, N, n, L, b = shape
+    x, w, g = make_inputs(Layer("t", B, C, K, N, n), seed=67 + sum(shape))
+
+    def two(e):
+        return np.float32(2.0**e)
+
+    exponents = {"x": (-124, 60, 20), "w": (60, -118, 20), "g": (20, 60, -124)}
+    if which in exponents:
+        x, w, g = (a * two(e) for a, e in zip((x, w, g), exponents[which]))
+        check_whole(x, w, g, tiling=(L, b))
+        return
+    x *= two(-22)
+    if which == "channels":
+        x[:, 1::2] *= two(-102)
+        w[:, 1::2] *= two(102)
+    else:
+        x[1::2] *= two(-102)
+        g[1::2] *= two(102)
+    _, y, dx, dw = run_layer(x, w, g, tiling=(L, b))
+    axis = 1 if which == "channels" else 0
+    check_groups(y, oracle.conv_forward(x, w), 0 if which == "images" else 2)
+    check_groups(dx, oracle.conv_backward_data(g, w, N), axis)
+    check_groups(dw, oracle.conv_backward_filter(x, g, n), 1)
+
+
+@pytest.mark.parametrize("C", [5, 40])
+@pytest.mark.parametrize("L, b, n", [(16, 14, 3), (32, 28, 5)])
+def test_contraction_of_huge_values(gpu_lib, L, b, n, C):
+    """A bin that rounds past bf16's largest number (3.396e38 and up) and is
+    below fp32's."""
+    N = 2 * b
+    x, w, g = make_inputs(Layer("t", 1, C, 9, N, n), seed=73 + L)
+    x[:, :2], w, g = 3.4e38 / b**2, w * np.float32(2.0**-40), g * np.float32(2.0**-40)
+    check_whole(x, w, g, tiling=(L, b))
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+@pytest.mark.parametrize("shape", [(3, 6, 40, 60, 5, 16, 12), (8, 100, 200, 30, 3, 16, 14)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_contraction_of_infinities(gpu_lib, shape, value):
+    """One infinite or NaN input element makes the same results infinite or NaN
+    on the matrix cores as on the vector ALUs, and leaves the others alone."""
+    B, C, K, N, n, L, b = shape
+    x, w, g = make_inputs(Layer("t", B, C, K, N, n), seed=79 + sum(shape))
+    x[1, 2, b + 1, 3] = value
+    _, *mfma = run_layer(x, w, g, binding.CONTRACTION_MFMA, tiling=(L, b))
+    _, *valu = run_layer(x, w, g, binding.CONTRACTION_VALU, tiling=(L, b))
+    for name, a, c in zip(("y", "dx", "dw"), mfma, valu):
+        fine = np.isfinite(c)
+        assert np.array_equal(np.isfinite(a), fine), name
+        assert fine.all() if name == "dx" else not fine.all(), name
+        if fine.any():
+            assert relerr(np.where(fine, a, 0), np.where(fine, c, 0)) <= TOL, name
 
 
 @pytest.mark.parametrize("shape", [
