@@ -216,7 +216,9 @@ __device__ __forceinline__ constexpr int quad_at(int row, int q) {
 // matrix or past the reduction bound get an offset beyond the resource, which
 // the hardware reads as zero. Lane FIRST takes the first task, so that two
 // small operands are staged by different waves.
-template <bool ROW_CONTIG, int ROWS, int THREADS, int FIRST>
+// LONG: rows of any length that fits (ROW_CONTIG), past the 2^25 elements from
+// which offsets of 16 of them, also those past a short reduction, wrap.
+template <bool ROW_CONTIG, int ROWS, int THREADS, int FIRST, bool LONG>
 struct Operand {
   static constexpr int TASKS = ROWS * 4, PER = (TASKS + THREADS - 1) / THREADS;
   static constexpr bool WHOLE = TASKS % THREADS == 0;  // every lane has PER tasks
@@ -234,7 +236,8 @@ struct Operand {
     for (int i = 0; i < PER; ++i) {
       const int t = task(i), r = r0 + row_of(t), k = 4 * quad_of(t);
       const bool ok = r < nrows && (WHOLE || t < TASKS);
-      voff[i] = ok ? (ROW_CONTIG ? unsigned(k) * ld + unsigned(r) : unsigned(r) * ld + unsigned(k)) * 8u : kOutOfRange;
+      const unsigned e = !ROW_CONTIG ? unsigned(r) * ld + unsigned(k) : LONG ? unsigned(r) : unsigned(k) * ld + unsigned(r);
+      voff[i] = ok ? e * 8u : kOutOfRange;
     }
   }
 
@@ -242,14 +245,21 @@ struct Operand {
   // ke, from a matrix of `elems` elements at base. The resource starts at the
   // slice, so that the hardware's range check sees only the lane offsets
   // (ROW_CONTIG: it also ends at the reduction bound). An offset out of range
-  // stays so when 3 ld elements are added (ld < 2^25, see mfma_fits).
+  // stays so when 3 ld elements are added (ld < 2^25, or LONG, which adds
+  // nothing to it and nothing past the reduction).
   __device__ __forceinline__ void load(const float2* base, size_t elems, unsigned ld, int k0, int ke) {
     if (ROW_CONTIG) {
       const __amdgpu_buffer_rsrc_t rs = buffer_resource(base + size_t(k0) * ld, unsigned(ke - k0) * ld * 8u);
 #pragma unroll
       for (int i = 0; i < PER; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) v[i][j] = buffer_load_f2(rs, voff[i] + unsigned(j) * ld * 8u);
+        for (int j = 0; j < 4; ++j) {
+          const int k = 4 * quad_of(task(i)) + j;
+          const bool in = voff[i] != kOutOfRange && k < ke - k0;
+          v[i][j] = buffer_load_f2(rs, !LONG ? voff[i] + unsigned(j) * ld * 8u
+                                       : in  ? voff[i] + unsigned(k) * ld * 8u
+                                             : kOutOfRange);
+        }
     } else {
       const __amdgpu_buffer_rsrc_t rs = buffer_resource(base + k0, unsigned(elems - size_t(k0)) * 8u);
 #pragma unroll
@@ -349,7 +359,7 @@ constexpr size_t mfma_lds_bytes(int TM, int TN) { return size_t(TM + TN) * 4 * 1
 // that it runs at. The large-kernel layer's three products take 0.78, 0.69
 // and 0.70 ms against 0.85, 0.86 and 0.74 on the fp32 matrix cores, those of
 // 128 channels at 56 x 56 0.21 against 0.28 ms.
-template <int WM, int WN, int MB, int NB, bool AT, bool AC, bool BT>
+template <int WM, int WN, int MB, int NB, bool AT, bool AC, bool BT, bool LONG>
 __global__ void __launch_bounds__(64 * WM * WN, 2) cgemm_mfma_kernel(GemmParams p, unsigned ntiles) {
   constexpr int TM = 16 * WM * MB, TN = 16 * WN * NB, THREADS = 64 * WM * WN;
   constexpr int QA = TM * 4, QB = TN * 4;  // quads per piece
@@ -372,8 +382,8 @@ __global__ void __launch_bounds__(64 * WM * WN, 2) cgemm_mfma_kernel(GemmParams 
   MfmaTile nx = cur;
   int lkk = ck;
 
-  Operand<AT, TM, THREADS, 0> sa;
-  Operand<!BT, TN, THREADS, (TM * 4) % THREADS> sb;
+  Operand<AT, TM, THREADS, 0, LONG> sa;
+  Operand<!BT, TN, THREADS, (TM * 4) % THREADS, LONG> sb;
   auto set_tile = [&](const MfmaTile& t) {
     sa.set_tile(t.m0, p.M, unsigned(p.lda));
     sb.set_tile(t.n0, p.N, unsigned(p.ldb));
@@ -605,7 +615,7 @@ __global__ void __launch_bounds__(64 * WM * WN, 2) cgemm_mfma_kernel(GemmParams 
   }
 }
 
-template <int WM, int WN, int MB, int NB, bool AT, bool AC, bool BT>
+template <int WM, int WN, int MB, int NB, bool AT, bool AC, bool BT, bool LONG = false>
 hipError_t launch_mfma_shape(const GemmParams& p, hipStream_t s) {
   constexpr int TM = 16 * WM * MB, TN = 16 * WN * NB, threads = 64 * WM * WN;
   constexpr size_t lds = mfma_lds_bytes(TM, TN);
@@ -613,7 +623,7 @@ hipError_t launch_mfma_shape(const GemmParams& p, hipStream_t s) {
                                    unsigned(p.nsplit) * unsigned(p.F);
   if (tiles == 0) return hipSuccess;
   if (tiles > 0xffffffffull) return hipErrorInvalidValue;
-  auto kern = cgemm_mfma_kernel<WM, WN, MB, NB, AT, AC, BT>;
+  auto kern = cgemm_mfma_kernel<WM, WN, MB, NB, AT, AC, BT, LONG>;
   hipError_t e = lds > 65536 ? tile::allow_lds(kern, lds) : hipSuccess;
   if (e != hipSuccess) return e;
   // resident workgroups of this instantiation, queried once per device
@@ -662,9 +672,17 @@ inline double mfma_estimate(const GemmParams& p, int TM, int TN, int occ) {
   return std::max(std::max(1.0, rounds) * work, std::ceil(tiles / (256 * occ)) * chain);
 }
 
+// Row-contiguous operands with rows under 2^25 elements: the offsets of 16
+// reduction indices fit 32 bits.
+bool rows_short(const GemmParams& p) {
+  const long lim = 1l << 25;
+  return (!p.a_trans || p.lda < lim) && (p.b_trans || p.ldb < lim);
+}
+
 // The tile shape with the least estimated time; `occ` by LDS and registers.
 template <bool AT, bool AC, bool BT>
 hipError_t launch_mfma(const GemmParams& p, hipStream_t s) {
+  if (!rows_short(p)) return launch_mfma_shape<1, 4, 1, 2, AT, AC, BT, true>(p, s);
   struct Shape {
     int tm, tn, occ;
     hipError_t (*launch)(const GemmParams&, hipStream_t);
@@ -704,6 +722,13 @@ hipError_t launch(Kern kern, const GemmParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
+// The matrix-core path reads each bin's operands and writes its result through
+// 32-bit byte offsets.
+bool mfma_addressable(const GemmParams& p) {
+  const size_t lim = size_t(1) << 28;
+  return p.a_fstride < lim && p.b_fstride < lim && p.c_fstride < lim && size_t(p.M) * size_t(p.ldc) < lim;
+}
+
 }  // namespace
 
 hipError_t launch_cgemm_valu(const GemmParams& p, hipStream_t s) {
@@ -723,7 +748,7 @@ hipError_t launch_cgemm_valu(const GemmParams& p, hipStream_t s) {
 
 hipError_t launch_cgemm_mfma(const GemmParams& p, hipStream_t s) {
   if (p.kchunk % kKC != 0 && p.nsplit > 1) return hipErrorInvalidValue;
-  if (!mfma_fits(p)) return hipErrorInvalidValue;
+  if (!mfma_addressable(p)) return hipErrorInvalidValue;
   if (p.a_trans && !p.a_conj && !p.b_trans && !p.b_conj) return launch_mfma<true, false, false>(p, s);
   if (!p.a_trans && p.a_conj && !p.b_trans && !p.b_conj) return launch_mfma<false, true, false>(p, s);
   if (!p.a_trans && p.a_conj && p.b_trans && !p.b_conj) return launch_mfma<false, true, true>(p, s);
@@ -731,14 +756,6 @@ hipError_t launch_cgemm_mfma(const GemmParams& p, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
-// The matrix-core path reads each bin's operands through 32-bit byte offsets;
-// where the rows are contiguous, offsets of up to 16 reduction indices, also
-// of those past a short reduction, must not wrap.
-bool mfma_fits(const GemmParams& p) {
-  const size_t lim = size_t(1) << 28;
-  const long row_lim = 1l << 25;
-  return p.a_fstride < lim && p.b_fstride < lim && p.c_fstride < lim && size_t(p.M) * size_t(p.ldc) < lim &&
-         (!p.a_trans || p.lda < row_lim) && (p.b_trans || p.ldb < row_lim);
-}
+bool mfma_fits(const GemmParams& p) { return mfma_addressable(p) && rows_short(p); }
 
 }  // namespace oaa

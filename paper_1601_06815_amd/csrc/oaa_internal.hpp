@@ -261,8 +261,10 @@ constexpr int kNarrowMaxC = 4;
 hipError_t launch_cgemm_narrow(const GemmParams& p, hipStream_t s);
 bool narrow_supported(const GemmParams& p);
 // Whether the matrix-core engine can address its operands and result with
-// 32-bit offsets (each bin's matrices under 2^28 complex elements); the
-// automatic choice takes it wherever it can and C > kNarrowMaxC.
+// 32-bit offsets (each bin's matrices under 2^28 complex elements) and has the
+// choice of its tile shapes (rows under 2^25 where they are contiguous; it
+// takes longer ones on one shape); the automatic choice takes it wherever this
+// holds and C > kNarrowMaxC.
 bool mfma_fits(const GemmParams& p);
 
 }  // namespace oaa

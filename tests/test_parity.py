@@ -205,6 +205,26 @@ def test_contraction_of_huge_values(gpu_lib, L, b, n, C):
     check_whole(x, w, g, tiling=(L, b))
 
 
+def test_matrix_core_long_rows(gpu_lib):
+    """More than 2^25 tiles per channel (rows of the per-bin matrices whose
+    offsets of 16 pass 32 bits) through the forced matrix-core contraction:
+    kernels of one element, whose results are sums of scaled planes."""
+    B, C, K, N, n = 1, 2, 3, 11586, 1
+    plan = binding.Plan(B, C, K, N, n, device=DEV, contraction=binding.CONTRACTION_MFMA, tiling=(2, 2))
+    assert plan.geometry["P"] > 1 << 25
+    gen = torch.Generator(device=DEV).manual_seed(83)
+    x = torch.rand((B, C, N, N), generator=gen, device=DEV) * 2 - 1
+    w = torch.randn((K, C, n, n), generator=gen, device=DEV)
+    y = plan.forward(x, w)
+    for k in range(K):
+        ref = sum(w[k, c, 0, 0].double() * x[0, c].double() for c in range(C))
+        assert float((y[0, k].double() - ref).abs().max() / ref.abs().max()) <= TOL
+    dx = plan.backward_data(y, w)
+    for c in range(C):
+        ref = sum(w[k, c, 0, 0].double() * y[0, k].double() for k in range(K))
+        assert float((dx[0, c].double() - ref).abs().max() / ref.abs().max()) <= TOL
+
+
 @pytest.mark.parametrize("value", [np.inf, np.nan])
 @pytest.mark.parametrize("shape", [(3, 6, 40, 60, 5, 16, 12), (8, 100, 200, 30, 3, 16, 14)],
                          ids=lambda s: "x".join(map(str, s)))
