@@ -503,17 +503,20 @@ hipError_t launch_inv_mode(BigInvParams p, hipStream_t s) {
   return hipGetLastError();
 }
 
+// The modes that a side is asked for: at 32 the overlap-adds (wide_overlap)
+// only, its crops being the other kernels'; at 64 the scratch is used where
+// OAA_TWO_STEP_MIN_L is set to it.
 template <int L>
 hipError_t launch_inv(const BigInvParams& p, hipStream_t s) {
-  switch (p.overlap) {
-    case 0: return launch_inv_mode<L, 0>(p, s);
-    case 1: return launch_inv_mode<L, 1>(p, s);
-    case 2: return launch_inv_mode<L, 2>(p, s);
-    case 3:
-      if constexpr (L <= 64) return launch_inv_mode<L, 3>(p, s);
-      return hipErrorInvalidValue;
-    default: return hipErrorInvalidValue;
+  if (p.overlap == 1) return launch_inv_mode<L, 1>(p, s);
+  if constexpr (L <= 64) {
+    if (p.overlap == 3) return launch_inv_mode<L, 3>(p, s);
   }
+  if constexpr (L >= 64) {
+    if (p.overlap == 0) return launch_inv_mode<L, 0>(p, s);
+    if (p.overlap == 2) return launch_inv_mode<L, 2>(p, s);
+  }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace
