@@ -24,9 +24,9 @@
 //    taken again in fp32 multiply-adds.
 #include <algorithm>
 #include <atomic>
-#include <cmath>
 
 #include "buffer_io.hpp"
+#include "mfma_tiles.hpp"
 #include "oaa_internal.hpp"
 #include "tile_common.hpp"
 
@@ -35,7 +35,7 @@ namespace oaa {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kKC = 16;  // reduction depth of one LDS slice
+constexpr int kKC = kMfmaSlice;  // reduction depth of one LDS slice
 
 // A ROWS x kKC slice of an operand whose element (row, k) is stored at
 // X[k*ld + row] (ROW_CONTIG) or X[row*ld + k]; loads are coalesced along the
@@ -645,33 +645,6 @@ hipError_t launch_mfma_shape(const GemmParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Estimated time (ns) of a contraction on TM x TN tiles of which a CU holds
-// `occ`: the larger of
-//  * a CU's work on its tiles (matrix products of the slices; the split of the
-//    operands, 11 vector instructions per element; a barrier per slice; the
-//    result stores);
-//  * the chain of one tile (a load's latency per slice, its products and
-//    stores), times the rounds of resident tiles.
-// The rates are a fixed calibration against sweeps over the tile shapes: the
-// large-kernel layer, 128 channels at 56 x 56, and layers of 5 to 138 channels.
-// Within it the shapes rank as they measured, in us with the launch: 64 x 144 x
-// 64 over 130 bins, 64 x 32 tiles 9.4 (estimated 6.0), 64 x 64 9.5 (7.5),
-// 64 x 96 11.9 (8.9), 128 x 64 13.4 (10.3); 48 x 64 x 64 over 514 bins, 64 x 64
-// 12 (8.2), 32 x 64 13 (9.5), 96 x 64 18 (11.6); 256 x 288 x 96 over 2050 bins,
-// 128 x 96 779 (730), 128 x 64 814 (842), 96 x 96 821 (834), 64 x 64 1030 (917).
-inline double mfma_estimate(const GemmParams& p, int TM, int TN, int occ) {
-  const double tiles = double((p.M + TM - 1) / TM) * ((p.N + TN - 1) / TN) * p.nsplit * p.F;
-  const double slices = (std::min(p.Kr, p.kchunk) + kKC - 1) / kKC;
-  const double area = double(TM) * TN;
-  const double work = slices * (0.149 * area + 1.3 * (TM + TN) + 60) + 0.15 * area + 100;
-  // 512 lanes (a CU to themselves) have half the products and stores per wave,
-  // and part of a round is half as good for them
-  const double lane = occ == 1 ? 0.5 * area : area;
-  const double chain = slices * (0.1 * lane + 900) + 0.3 * lane + 1000;
-  const double rounds = occ == 1 ? 0.5 * (tiles / 256 + std::ceil(tiles / 256)) : tiles / 256;
-  return std::max(std::max(1.0, rounds) * work, std::ceil(tiles / (256 * occ)) * chain);
-}
-
 // Row-contiguous operands with rows under 2^25 elements: the offsets of 16
 // reduction indices fit 32 bits.
 bool rows_short(const GemmParams& p) {
@@ -679,40 +652,22 @@ bool rows_short(const GemmParams& p) {
   return (!p.a_trans || p.lda < lim) && (p.b_trans || p.ldb < lim);
 }
 
-// The tile shape with the least estimated time; `occ` by LDS and registers.
+// The tile shape with the least estimated time.
 template <bool AT, bool AC, bool BT>
 hipError_t launch_mfma(const GemmParams& p, hipStream_t s) {
   if (!rows_short(p)) return launch_mfma_shape<1, 4, 1, 2, AT, AC, BT, true>(p, s);
-  struct Shape {
-    int tm, tn, occ;
-    hipError_t (*launch)(const GemmParams&, hipStream_t);
-  };
-  static constexpr Shape kShapes[] = {
-      {16, 64, 5, launch_mfma_shape<1, 4, 1, 1, AT, AC, BT>},
-      {16, 128, 2, launch_mfma_shape<1, 4, 1, 2, AT, AC, BT>},
-      {64, 16, 5, launch_mfma_shape<4, 1, 1, 1, AT, AC, BT>},
-      {32, 32, 6, launch_mfma_shape<2, 2, 1, 1, AT, AC, BT>},
-      {32, 64, 4, launch_mfma_shape<2, 2, 1, 2, AT, AC, BT>},
-      {64, 32, 4, launch_mfma_shape<2, 2, 2, 1, AT, AC, BT>},
-      {64, 64, 3, launch_mfma_shape<2, 2, 2, 2, AT, AC, BT>},
-      {96, 64, 2, launch_mfma_shape<2, 2, 3, 2, AT, AC, BT>},
-      {64, 96, 2, launch_mfma_shape<2, 2, 2, 3, AT, AC, BT>},
-      {128, 64, 2, launch_mfma_shape<2, 2, 4, 2, AT, AC, BT>},
-      {96, 96, 2, launch_mfma_shape<2, 2, 3, 3, AT, AC, BT>},
-      {128, 96, 1, launch_mfma_shape<4, 2, 2, 3, AT, AC, BT>},
-      {96, 128, 1, launch_mfma_shape<2, 4, 3, 2, AT, AC, BT>},
-      {128, 128, 1, launch_mfma_shape<2, 4, 4, 2, AT, AC, BT>},
-  };
-  const Shape* best = nullptr;
-  double least = 0;
-  for (const Shape& sh : kShapes) {
-    const double t = mfma_estimate(p, sh.tm, sh.tn, sh.occ);
-    if (!best || t < least) {
-      best = &sh;
-      least = t;
-    }
-  }
-  return best->launch(p, s);
+  using Launch = hipError_t (*)(const GemmParams&, hipStream_t);
+  static constexpr Launch kLaunch[] = {
+      launch_mfma_shape<1, 4, 1, 1, AT, AC, BT>, launch_mfma_shape<1, 4, 1, 2, AT, AC, BT>,
+      launch_mfma_shape<4, 1, 1, 1, AT, AC, BT>, launch_mfma_shape<2, 2, 1, 1, AT, AC, BT>,
+      launch_mfma_shape<2, 2, 1, 2, AT, AC, BT>, launch_mfma_shape<2, 2, 2, 1, AT, AC, BT>,
+      launch_mfma_shape<2, 2, 2, 2, AT, AC, BT>, launch_mfma_shape<2, 2, 3, 2, AT, AC, BT>,
+      launch_mfma_shape<2, 2, 2, 3, AT, AC, BT>, launch_mfma_shape<2, 2, 4, 2, AT, AC, BT>,
+      launch_mfma_shape<2, 2, 3, 3, AT, AC, BT>, launch_mfma_shape<4, 2, 2, 3, AT, AC, BT>,
+      launch_mfma_shape<2, 4, 3, 2, AT, AC, BT>, launch_mfma_shape<2, 4, 4, 2, AT, AC, BT>,
+  };  // in the order of kMfmaTiles
+  static_assert(sizeof kLaunch / sizeof kLaunch[0] == sizeof kMfmaTiles / sizeof kMfmaTiles[0], "one per shape");
+  return kLaunch[mfma_tile_choice(p.M, p.N, p.Kr, p.kchunk, p.nsplit, p.F)](p, s);
 }
 
 template <int TM, int TN, class Kern>

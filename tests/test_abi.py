@@ -238,6 +238,42 @@ def test_binding_raises_with_detail(lib):
     assert "exceeds" in str(e.value)
 
 
+def test_matrix_core_tile_choice(lib, tmp_path):
+    """The tile shapes (csrc/mfma_tiles.hpp, plain C++) that the contractions of
+    the GPU tests' layers take are those that the tests name, and every shape is
+    among them."""
+    import shutil
+    import subprocess
+
+    from tests.test_parity import MATRIX_CORE
+
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("no g++")
+    src, exe = tmp_path / "t.cpp", tmp_path / "t"
+    src.write_text('#include "mfma_tiles.hpp"\n#include <cstdio>\n'
+                   'int main() { for (auto& s : oaa::kMfmaTiles) std::printf("%dx%d\\n", s.tm, s.tn);\n'
+                   '  int M, N, Kr, c, s, F;\n'
+                   '  while (std::scanf("%d%d%d%d%d%d", &M, &N, &Kr, &c, &s, &F) == 6)\n'
+                   '    std::printf("%d\\n", oaa::mfma_tile_choice(M, N, Kr, c, s, F)); }\n')
+    subprocess.run([cxx, "-std=c++17", "-I", build.CSRC, str(src), "-o", str(exe)], check=True)
+    wanted, jobs = [], []
+    for (B, C, K, N, n, L, b), tiles in MATRIX_CORE.items():
+        plan = binding.oaa_plan_create_tiled(B, C, K, N, n, L, b)
+        g = binding.oaa_plan_geometry(plan)
+        binding.oaa_plan_destroy(plan)
+        F, BP, split = (L // 2 + 1) ** 2 + (L // 2 - 1) ** 2, B * g["P"], g["split"]
+        chunks = [c for c in range(16, BP + 32, 16) if -(-BP // c) == split]  # one of these
+        calls = [(tiles[0], (K, BP, C, C, 1, F)), (tiles[1], (C, BP, K, K, 1, F))]
+        calls += [(tiles[2], (C, K, BP, c, split, F)) for c in chunks]
+        wanted += [t for t, _ in calls]
+        jobs += [" ".join(map(str, j)) for _, j in calls]
+    out = subprocess.run([str(exe)], input="\n".join(jobs), capture_output=True, text=True, check=True).stdout.split()
+    names, got = out[:-len(jobs)], out[-len(jobs):]
+    assert [names[int(i)] for i in got] == wanted
+    assert set(wanted) == set(names)
+
+
 def test_twiddle_table_matches_libm(tmp_path):
     """The compile-time twiddles (csrc/twiddle.hpp, plain C++) against the C
     library's cos/sin in double, rounded to float."""
@@ -252,7 +288,7 @@ def test_twiddle_table_matches_libm(tmp_path):
                    'template <int L> void dump() { for (int k = 0; k < L; ++k) '
                    'std::printf("%d %d %.9e %.9e\\n", L, k, (double)oaa::tw::kTable<L>.c[k], '
                    '(double)oaa::tw::kTable<L>.s[k]); }\n'
-                   'int main() { dump<2>(); dump<4>(); dump<8>(); dump<16>(); dump<32>(); dump<64>(); }\n')
+                   'int main() { dump<2>(); dump<4>(); dump<8>(); dump<16>(); dump<32>(); dump<64>(); dump<128>(); }\n')
     exe = tmp_path / "tw"
     csrc = os.path.join(os.path.dirname(build.LIB_PATH), "csrc")
     subprocess.run([cxx, "-std=c++17", "-O1", "-I", csrc, str(src), "-o", str(exe)], check=True)

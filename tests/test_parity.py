@@ -87,33 +87,45 @@ def test_contraction_variants(gpu_lib, contraction, shape):
 
 
 @pytest.mark.parametrize("shape", [
-    (4, 40, 128, 60, 9, 32, 24),    # forward rows (K = 128) in 128-row tiles
-    (4, 96, 40, 60, 9, 32, 24),     # error-propagation rows (C = 96) in 96-row tiles
+    (4, 40, 128, 60, 9, 32, 24),    # 128 rows (forward), 128 deep (error propagation)
+    (4, 96, 40, 60, 9, 32, 24),     # 96 deep (forward), 96 rows (error propagation)
     (10, 32, 64, 100, 16, 64, 49),  # B P = 90 columns: 64 x 96 tiles (forward)
 ], ids=lambda s: "x".join(map(str, s)))
 def test_matrix_core_tile_shapes(gpu_lib, shape):
-    """The matrix-core contraction's tile shapes (128 x 64, 96 x 64, 64 x 96),
-    forced, against the oracle, compared whole."""
+    """The matrix-core contraction, forced, against the oracle, compared whole,
+    where extents are a tile's or just short of it."""
     B, C, K, N, n, L, b = shape
     x, w, g = make_inputs(Layer("t", B, C, K, N, n), seed=31 + sum(shape))
     check_whole(x, w, g, binding.CONTRACTION_MFMA, tiling=(L, b))
 
 
-@pytest.mark.parametrize("shape", [
-    (2, 5, 9, 20, 3, 16, 14),       # one slice or less of every reduction: 16 x 64 tiles
-    (5, 19, 27, 61, 9, 32, 24),     # odd sizes, ragged reductions: 32 x 32
-    (3, 6, 40, 60, 5, 16, 12),      # few rows; split reduction
-    (8, 5, 7, 60, 3, 16, 14),       # every extent below a tile's
-    (30, 7, 150, 20, 3, 8, 6),      # 64 x 96, 16 x 64
-    (30, 150, 7, 20, 3, 8, 6),      # 64 x 16
-    (19, 78, 106, 15, 3, 8, 6),     # 16 x 128
-    (16, 64, 64, 30, 3, 16, 14),    # 64 x 32, 32 x 64
-    (8, 100, 200, 30, 3, 16, 14),   # 96 x 96, 64 x 32, 128 x 64
-    (40, 96, 96, 30, 3, 16, 14),    # 96 x 64, 96 x 96
-    (8, 256, 96, 60, 5, 32, 28),    # 96 x 96, 64 x 96, 128 x 96
-    (10, 96, 256, 60, 9, 32, 24),   # 96 x 128
-    (1, 97, 197, 49, 16, 64, 49),   # one column; 128 x 128
-], ids=lambda s: "x".join(map(str, s)))
+# Layers and the tile shapes that their three products take (forward, error
+# propagation, weight gradient): every shape among them, which the host tests
+# check against the choice.
+MATRIX_CORE = {
+    # one slice or less of every reduction
+    (2, 5, 9, 20, 3, 16, 14): ("16x64", "16x64", "16x64"),
+    # odd sizes, ragged reductions
+    (5, 19, 27, 61, 9, 32, 24): ("32x32", "32x32", "32x32"),
+    # few rows; split reduction
+    (3, 6, 40, 60, 5, 16, 12): ("16x64", "16x64", "16x64"),
+    # every extent below a tile's
+    (8, 5, 7, 60, 3, 16, 14): ("16x64", "16x64", "16x64"),
+    (30, 7, 150, 20, 3, 8, 6): ("64x96", "16x64", "16x64"),
+    (30, 150, 7, 20, 3, 8, 6): ("16x64", "64x96", "64x16"),
+    (19, 78, 106, 15, 3, 8, 6): ("16x64", "16x64", "16x128"),
+    (16, 64, 64, 30, 3, 16, 14): ("64x32", "64x32", "32x64"),
+    (8, 64, 64, 60, 3, 16, 14): ("64x64", "64x64", "64x64"),
+    (8, 100, 200, 30, 3, 16, 14): ("96x96", "64x32", "128x64"),
+    (40, 96, 96, 30, 3, 16, 14): ("96x64", "96x64", "96x96"),
+    (8, 256, 96, 60, 5, 32, 28): ("96x96", "64x96", "128x96"),
+    (10, 96, 256, 60, 9, 32, 24): ("64x96", "96x96", "96x128"),
+    # one column
+    (1, 97, 197, 49, 16, 64, 49): ("64x16", "64x16", "128x128"),
+}
+
+
+@pytest.mark.parametrize("shape", MATRIX_CORE, ids=lambda s: "x".join(map(str, s)))
 def test_matrix_core_split(gpu_lib, shape):
     """The contraction on three bf16 pieces per value, over its tile shapes,
     against the oracle; and scaling an input by a power of two, to magnitudes
