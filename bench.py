@@ -87,13 +87,13 @@ def traffic_key(workload, geo, stage):
 
 
 SHARED_SOURCES = ("oaa_plan.cpp", "oaa_internal.hpp", "tile_common.hpp", "fft_core.hpp", "twiddle.hpp",
-                  "buffer_io.hpp")
+                  "buffer_io.hpp", "mfma_tiles.hpp")
 
 
 def source_digest(fname):
     """Digest of a kernel's source file(s) ("a.hip+b.hip" for a stage of two
-    kernels) together with the headers they share and the plan code that
-    picks their launch shape."""
+    kernels) together with the headers they share and the code that picks
+    their launch shape."""
     h = hashlib.sha256()
     for f in tuple(fname.split("+")) + SHARED_SOURCES:
         h.update(open(os.path.join(ROOT, "paper_1601_06815_amd", "csrc", f), "rb").read())
@@ -188,7 +188,7 @@ LIB_KERNELS = ("tile_rfft2_kernel", "window_rfft2_kernel", "window_rows_rfft2_ke
 def stage_sequence(geo):
     """The stage of each kernel launch of one training step, in launch order
     (the fused passes launch one kernel per pass; the two-step overlap-add at
-    L = 128, planes of more than two tiles, adds a gather kernel)."""
+    L = 128, planes of more than one tile, adds a gather kernel)."""
     if geo.get("fused"):
         return ["w_spectrum", "x_spectrum", "fwd_inverse", "bwd_data_product", "bwd_filter_product",
                 "bwd_filter_inverse"]

@@ -201,7 +201,7 @@ __device__ __forceinline__ void split3(float2 x, unsigned& p0, unsigned& p1, uns
 
 // LDS image of an operand's ROWS x kKC slice, one per piece: rows of four
 // 16-byte quads, quad q holding reduction indices 4q .. 4q + 3 as packed
-// complex pieces, stored at quad q ^ ((row / 4) % 4) of the row. The 16
+// complex pieces, stored at quad q ^ ((row / 2) % 4) ^ ((row / 8) % 2) of the row. The 16
 // lanes that read one quad of 16 consecutive rows, and the lanes that write
 // it, then fall on all 64 banks.
 __device__ __forceinline__ constexpr int quad_at(int row, int q) {
@@ -353,12 +353,16 @@ constexpr size_t mfma_lds_bytes(int TM, int TN) { return size_t(TM + TN) * 4 * 1
 // partial results of 65 x 56 went from 2.9e-7 relative error to 1.6e-7 (2.0e-7
 // on the vector units), that of 128 channels at 56 x 56 from 3.2e-7 to 1.9e-7.
 //
-// Bound by power at large sizes: the clock falls to 1.5 - 1.9 GHz, and
-// neither deeper prefetch, nor three workgroups per CU on a single buffer,
-// nor the split interleaved with the products moved the 1.05 PFLOP/s of bf16
-// that it runs at. The large-kernel layer's three products take 0.78, 0.69
-// and 0.70 ms against 0.85, 0.86 and 0.74 on the fp32 matrix cores, those of
-// 128 channels at 56 x 56 0.21 against 0.28 ms.
+// Bound by issue at large sizes. Over the large-kernel layer's three products
+// the matrix units are busy 39 - 44 % of the cycles and the other vector
+// instructions (the split, the swaps and signs of the packed operand, the
+// slices' sums) take another 40 - 43 %; the waves, two per SIMD, wait for their
+// turn to issue 35 - 44 % of the time and for data or a barrier 15 - 26 %. The
+// clock is at 2.0 - 2.1 GHz. Neither deeper prefetch, nor three workgroups per CU
+// on a single buffer, nor the split interleaved with the products moved the
+// 1.05 PFLOP/s of bf16 that it runs at. The three products take 0.79, 0.72 and
+// 0.73 ms against 0.88, 0.88 and 0.77 on the fp32 matrix cores, those of 128
+// channels at 56 x 56 0.25 against 0.29 ms (both in one run).
 template <int WM, int WN, int MB, int NB, bool AT, bool AC, bool BT, bool LONG>
 __global__ void __launch_bounds__(64 * WM * WN, 2) cgemm_mfma_kernel(GemmParams p, unsigned ntiles) {
   constexpr int TM = 16 * WM * MB, TN = 16 * WN * NB, THREADS = 64 * WM * WN;

@@ -10,7 +10,8 @@ namespace oaa {
 
 constexpr int kMfmaSlice = 16;  // reduction depth of one LDS slice
 
-// Rows and columns of a tile, and the tiles a CU holds by LDS and registers.
+// Rows and columns of a tile, and the tiles a CU holds by LDS and registers
+// (32 x 32 by LDS: its registers leave five).
 struct MfmaTileShape {
   int tm, tn, occ;
 };
@@ -25,7 +26,7 @@ constexpr MfmaTileShape kMfmaTiles[] = {
 //    operands, 12 vector instructions per element; a barrier per slice; the
 //    result stores);
 //  * the chain of one tile (a load's latency per slice, its products and
-//    stores), times the rounds of resident tiles.
+//    stores), times the rounds of resident tiles on 256 CUs.
 // The rates are a fixed calibration against sweeps over the tile shapes: the
 // large-kernel layer, 128 channels at 56 x 56, and layers of 5 to 138 channels.
 // Within it the shapes rank as they measured, in us with the launch: 64 x 144 x

@@ -41,13 +41,16 @@
 #endif
 
 
-// Weight-gradient split: enough partial products that the tiled contraction
-// has at least this many tiles, a little over two rounds of its 512 resident
-// workgroups. More partial sums balance the rounds better but cost the
-// inverse one more read of the whole weight-gradient spectrum each: measured,
-// 1152 gives the 56 x 56 layer 8 (11 cost 0.03 ms more) and the large-kernel
-// layer at L = 64 one (2 took 0.79 against 0.75 ms for the contraction, and
-// 0.19 ms more per step); overridable at build time for sweeps.
+// Weight-gradient split: enough partial products that the contraction has at
+// least this many tiles of 96 or 128 rows by 128 columns. More partial sums
+// spread it better but cost the inverse one more read of the whole
+// weight-gradient spectrum each. Measured when the contraction ran in fp32 on
+// the matrix cores, in such tiles, two workgroups per CU: 1152 gives the 56 x 56
+// layer 8 (11 cost 0.03 ms more) and the large-kernel layer at L = 64 one (2
+// took 0.79 against 0.75 ms for the contraction, and 0.19 ms more per step). On
+// bf16 pieces, in the tile shapes of mfma_tiles.hpp, the 56 x 56 layer's
+// contraction takes 219 us with 8 and 327 with one; the line has not been
+// measured anew. Overridable at build time for sweeps.
 #ifndef OAA_SPLIT_TILES
 #define OAA_SPLIT_TILES 1152
 #endif
@@ -527,11 +530,14 @@ oaa_status_t run_gemm(const Ctx& cx, oaa::GemmParams& g, oaa_stage_t stage, cons
 // kernel, read by the next) and the planes once each way, at a rate per
 // transform side that runs of few tiles per plane lower; the contractions
 // run on the matrix cores (C, K >= 32; three products, six flops per complex
-// multiply-add) or stream their spectra (few channels). The rates are a fixed
-// calibration against the measured training steps of the large layers
-// (transform stages at 3.5, 2.5, 2.1 and 1.05 TB/s for L <= 16, 32, 64 and
-// 128; 110 TFLOP/s executed on the matrix cores; 4 TB/s streaming), not a
-// measured search.
+// multiply-add) or stream their spectra. The rates are a fixed calibration
+// against training steps of the large layers (transform stages at 3.5, 2.5, 2.1
+// and 1.05 TB/s for L <= 16, 32, 64 and 128; 110 TFLOP/s executed on the matrix
+// cores; 4 TB/s streaming), not a measured search, and it was made on earlier
+// kernels: the contraction in fp32 on the matrix cores from 32 channels up,
+// where all layers of more than four channels now run it on bf16 pieces, and
+// side-128 transforms half as fast as today's. It ranks tilings; the present
+// kernels' times are not its.
 double step_time_estimate(int B, int C, int K, int N, int n, int L, int T) {
   const double M = N - n + 1, BP = double(B) * T * T, Fu = oaa::unique_bins(L);
   const double spec = Fu * BP * 8;  // one spectrum channel, bytes
@@ -903,8 +909,8 @@ oaa_status_t oaa_plan_create_method(oaa_plan_t* out, int B, int C, int K, int N,
 
   // split of the weight-gradient reduction over B*P, shared by every
   // contraction engine (the inverse adds the partial sums):
-  //  * tiled engines: 96- or 128-row by 128-column tiles, two workgroups per
-  //    CU, about OAA_SPLIT_TILES tiles; chunks of 16 tiles;
+  //  * tiled engines: about OAA_SPLIT_TILES tiles of 96 or 128 rows by 128
+  //    columns, whatever shape the launch takes; chunks of 16 tiles;
   //  * few input channels (the streaming engine): about 2048 workgroups of 64
   //    kernels, chunks of at least 1024 tiles, a multiple of 128.
   long long split, quantum;
