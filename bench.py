@@ -321,7 +321,8 @@ def summarize_counters(layer, run_dir, steps=2, method="oaa"):
     work = stage_work(ly, geo)
     name = "overlap-save, h" if geo.get("method") else "b"
     print(f"## {layer}, L={geo['L']} {name}={geo['b']} (mean over the last {steps} steps)")
-    print(f"{'stage':20s} {'kernel':44s} " + " ".join(f"{c[:24]:>24s}" for c in names))
+    heads = [c if len(c) <= 24 else f"{c[:8]}..{c[-14:]}" for c in names]
+    print(f"{'stage':20s} {'kernel':44s} " + " ".join(f"{c:>24s}" for c in heads))
     path = os.path.join(PROFILE_DIR, "mfma.json")
     db = json.load(open(path)) if os.path.exists(path) else {}
     for stage in [st for st in STAGE_ORDER if st in staged]:
