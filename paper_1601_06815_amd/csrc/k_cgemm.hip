@@ -356,9 +356,9 @@ constexpr size_t mfma_lds_bytes(int TM, int TN) { return size_t(TM + TN) * 4 * 1
 // Bound by issue at large sizes. Over the large-kernel layer's three products
 // the matrix units are busy 39 - 44 % of the cycles and the other vector
 // instructions (the split, the swaps and signs of the packed operand, the
-// slices' sums) take another 40 - 43 %; the waves, two per SIMD, wait for their
+// slices' sums) take another 40 - 44 %; the waves, two per SIMD, wait for their
 // turn to issue 35 - 44 % of the time and for data or a barrier 15 - 26 %. The
-// clock is at 2.0 - 2.1 GHz. Neither deeper prefetch, nor three workgroups per CU
+// clock is at 2.0 - 2.2 GHz. Neither deeper prefetch, nor three workgroups per CU
 // on a single buffer, nor the split interleaved with the products moved the
 // 1.05 PFLOP/s of bf16 that it runs at. The three products take 0.79, 0.72 and
 // 0.73 ms against 0.88, 0.88 and 0.77 on the fp32 matrix cores, those of 128
