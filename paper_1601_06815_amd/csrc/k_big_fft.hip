@@ -338,8 +338,8 @@ __device__ __forceinline__ void overlap_plane_out(const BigInvParams& p, const f
 // transform's values live across the stores, and spill), pass 2 runs on the
 // row pairs that hold kept rows only, and the output pass applies the
 // rotation and the 1/L^2 scale. MODE: the kernel's pass 3 (0 crop, 1
-// overlap-add of one-group planes, 2 tiles to the scratch), fixed per instance
-// so that each carries only the registers of its own output code; SPLIT: more
+// overlap-add of one-group planes), fixed per instance so that each carries
+// only the registers of its own output code; SPLIT: more
 // than one partial spectrum to sum (the weight gradient's split), loaded in
 // batches of 16 rows so that the partial sums and the loads in flight fit
 // the registers.
@@ -453,33 +453,22 @@ __global__ void __launch_bounds__(512) big_irfft2_lane_kernel(BigInvParams p) {
       d0[2 * RI + s] = im[bitrev(s, L)];
     }
   };
-  // pass 3, MODE 0 and 2: the kept KR x KR of every tile, scaled, to its
-  // block (0) or to the scratch, tile after tile (2); a wave per tile
-  // (decoded once, wave-uniform), lanes over the block in row order
+  // pass 3, MODE 0: the kept KR x KR of every tile, scaled, to its block; a
+  // wave per tile (decoded once, wave-uniform), lanes over the block in row order
   auto crop = [&](int ch, int t0, int nq, int wave, int lane, int nwave, auto rotated) {
     constexpr bool ROT = decltype(rotated)::value;
     const float scale = 1.0f / float(L * L);
     const SmallDiv div_k(KR);
     for (int qq = wave; qq < nq; qq += nwave) {
       const float* lt = ldf + 2 * qq * TSZ;
-      int nrow = KR, ncol = KR;
-      float* ob;
-      int ostride;
-      if (MODE == 0) {
-        const int t = t0 + qq, img = t / P, pp = t - img * P;
-        const int pr = pp / p.T, qc = pp - pr * p.T;
-        nrow = min(KR, p.H - pr * p.pitch);
-        ncol = min(KR, p.H - qc * p.pitch);
-        ob = p.dst + ((size_t(img) * p.n_ch + ch) * p.H + pr * p.pitch) * p.H + qc * p.pitch;
-        ostride = p.H;
-      } else {
-        ob = p.tiles + ((size_t(ch) * tpc + t0 + qq) * KR) * KR;
-        ostride = KR;
-      }
+      const int t = t0 + qq, img = t / P, pp = t - img * P;
+      const int pr = pp / p.T, qc = pp - pr * p.T;
+      const int nrow = min(KR, p.H - pr * p.pitch), ncol = min(KR, p.H - qc * p.pitch);
+      float* ob = p.dst + ((size_t(img) * p.n_ch + ch) * p.H + pr * p.pitch) * p.H + qc * p.pitch;
       for (int e = lane; e < KR * nrow; e += 64) {
         const int rr = div_k(e), cc = e - rr * KR;
         const int sr = ROT ? (rr - rot) & (L - 1) : rr, sc = ROT ? (cc - rot) & (L - 1) : cc;
-        if (cc < ncol) ob[rr * ostride + cc] = lt[2 * sr * RI + sc] * scale;
+        if (cc < ncol) ob[rr * p.H + cc] = lt[2 * sr * RI + sc] * scale;
       }
     }
   };
@@ -630,8 +619,8 @@ hipError_t launch_big_inv_lane_O(const BigInvParams& p, size_t lds, long ngroups
   void (*kern)(BigInvParams) = nullptr;
   if (p.overlap == 0)
     kern = p.nsplit > 1 ? big_irfft2_lane_kernel<O32, 0, true> : big_irfft2_lane_kernel<O32, 0, false>;
-  else if (p.nsplit == 1)  // the overlap-add of forward spectra: one partial
-    kern = p.overlap == 1 ? big_irfft2_lane_kernel<O32, 1, false> : big_irfft2_lane_kernel<O32, 2, false>;
+  else if (p.overlap == 1 && p.nsplit == 1)  // the overlap-add of forward spectra: one partial
+    kern = big_irfft2_lane_kernel<O32, 1, false>;
   if (!kern) return hipErrorInvalidValue;
   const hipError_t e = allow_lds(kern, kBigLds);
   if (e != hipSuccess) return e;
@@ -664,8 +653,8 @@ hipError_t launch_big_inv(int L, BigInvParams p, hipStream_t s) {
       return launch_wide_irfft2(L, p, s);
     }
     if (!big_overlap_supported(L, p.T)) {
-      // keep every tile's KR x KR in the scratch, then add in a second kernel
-      if (!p.tiles || long(p.KR) * p.KR >= 65536) return hipErrorInvalidValue;
+      // side 128: keep every tile's KR x KR in the scratch, then add in a second kernel
+      if (L == Big::L || !p.tiles || long(p.KR) * p.KR >= 65536) return hipErrorInvalidValue;
       two_step = true;
       p.overlap = 2;
     }

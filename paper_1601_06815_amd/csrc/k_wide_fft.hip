@@ -504,8 +504,8 @@ hipError_t launch_inv_mode(BigInvParams p, hipStream_t s) {
 }
 
 // The modes that a side is asked for: at 32 the overlap-adds (wide_overlap)
-// only, its crops being the other kernels'; at 64 the scratch is used where
-// OAA_TWO_STEP_MIN_L is set to it.
+// only, its crops being the other kernels'; the scratch at 128 only, whose
+// planes of several tiles have no other kernel.
 template <int L>
 hipError_t launch_inv(const BigInvParams& p, hipStream_t s) {
   if (p.overlap == 1) return launch_inv_mode<L, 1>(p, s);
@@ -514,6 +514,8 @@ hipError_t launch_inv(const BigInvParams& p, hipStream_t s) {
   }
   if constexpr (L >= 64) {
     if (p.overlap == 0) return launch_inv_mode<L, 0>(p, s);
+  }
+  if constexpr (L == 128) {
     if (p.overlap == 2) return launch_inv_mode<L, 2>(p, s);
   }
   return hipErrorInvalidValue;

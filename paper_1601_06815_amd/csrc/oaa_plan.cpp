@@ -29,17 +29,11 @@
 #define OAA_BLOCKS_AS_WINDOWS 1
 #endif
 
-// Transform sides from which the tile-group kernels of k_big_fft.hip take
-// every transform, and from which their two-step overlap-add (tile results
-// through a scratch) serves planes of more tiles than a workgroup holds
-// (overridable at build time for comparisons).
+// Transform side from which the tile-group kernels of k_big_fft.hip take
+// every transform (overridable at build time for comparisons).
 #ifndef OAA_BIG_MIN_L
 #define OAA_BIG_MIN_L 64
 #endif
-#ifndef OAA_TWO_STEP_MIN_L
-#define OAA_TWO_STEP_MIN_L 128
-#endif
-
 
 // Weight-gradient split: enough partial products that the contraction has at
 // least this many tiles of 96 or 128 rows by 128 columns. More partial sums
@@ -196,6 +190,10 @@ oaa_status_t timed(const Ctx& cx, oaa_stage_t stage, const char* what, Fn&& laun
   p->records.push_back({int(stage), a, b});
   return OAA_OK;
 }
+
+// Side whose planes of more tiles than a workgroup holds are overlap-added in
+// two steps, tile results through a scratch: it has no other kernel for them.
+constexpr int kTwoStepL = 128;
 
 bool big_side(const oaa_plan_s* p) { return p->L >= OAA_BIG_MIN_L; }
 
@@ -632,7 +630,7 @@ oaa_status_t forward_pass(const Ctx& cx, const float* x, const float* w, float* 
     return big_inverse(cx, OAA_STAGE_FWD_INVERSE, "inverse transform + overlap-save crop",
                        region(cx, OAA_REGION_PRODUCT), 1, 0, y, p->B, p->K, p->M, p->b, 0, p->T, p->b,
                        (p->L - (p->n - 1)) & (p->L - 1), 0);
-  if (big_side(p) && (oaa::big_overlap_supported(p->L, p->T) || p->L >= OAA_TWO_STEP_MIN_L ||
+  if (big_side(p) && (oaa::big_overlap_supported(p->L, p->T) || p->L >= kTwoStepL ||
                       oaa::big_overlap_few(p->L, long(p->B) * p->K, p->T)))
     return big_inverse(cx, OAA_STAGE_FWD_INVERSE, "inverse transform + overlap-add", region(cx, OAA_REGION_PRODUCT),
                        1, 0, y, p->B, p->K, p->M, p->b, p->n - 1, p->T, p->b + p->n - 1, 0, 1);
@@ -701,7 +699,7 @@ oaa_status_t backward_data_pass(const Ctx& cx, const float* g, const float* w, f
   if (big_side(p) && p->method != OAA_METHOD_OVERLAP_SAVE)
     return big_inverse(cx, OAA_STAGE_BWD_DATA_INVERSE, "inverse transform + block crop", region(cx, OAA_REGION_PRODUCT),
                        1, 0, dx, p->B, p->C, p->N, p->b, 0, p->T, p->b, 0, 0);
-  if (big_side(p) && (oaa::big_overlap_supported(p->L, p->T) || p->L >= OAA_TWO_STEP_MIN_L ||
+  if (big_side(p) && (oaa::big_overlap_supported(p->L, p->T) || p->L >= kTwoStepL ||
                       oaa::big_overlap_few(p->L, long(p->B) * p->C, p->T)))
     return big_inverse(cx, OAA_STAGE_BWD_DATA_INVERSE, "inverse transform + overlap-add",
                        region(cx, OAA_REGION_PRODUCT), 1, 0, dx, p->B, p->C, p->N, p->b, 0, p->T, p->L, p->n - 1, 1);
@@ -954,10 +952,10 @@ oaa_status_t oaa_plan_create_method(oaa_plan_t* out, int B, int C, int K, int N,
   }
   // scratch of the overlap-add passes (the forward pass with overlap-add,
   // error propagation with overlap-save) whose planes hold more tiles than
-  // one workgroup keeps (from OAA_TWO_STEP_MIN_L; L = 128 has no other kernel)
+  // one workgroup keeps (kTwoStepL)
   p->tiles_off = off;
   p->tiles_size = 0;
-  if (L >= OAA_TWO_STEP_MIN_L && L >= OAA_BIG_MIN_L && !oaa::big_overlap_supported(L, T)) {
+  if (L >= kTwoStepL && !oaa::big_overlap_supported(L, T)) {
     p->tiles_size = method == OAA_METHOD_OVERLAP_ADD ? oaa::overlap_tile_bytes((long)B * K, T, b + n - 1)
                                                      : oaa::overlap_tile_bytes((long)B * C, T, L);
     off = align_up(off + p->tiles_size);
